@@ -77,7 +77,7 @@ struct sibfa_ctx_s {
   // cells
   int nc[3] = {1, 1, 1}, ncell = 1;
   int *cell_of = nullptr, *cell_count = nullptr, *cell_start = nullptr, *cursor = nullptr;
-  int4* cellmax = nullptr;   // per-cell list count maxima
+  int4* cellmax = nullptr;   // list count maxima per cell and slice
   int *perm = nullptr, *inv_perm = nullptr, *mol_count = nullptr, *mol_s = nullptr;
   int* scan_tmp = nullptr;
   // records
@@ -625,11 +625,12 @@ sibfa_status build_lists(sibfa_ctx c, Beside beside) {
     a.nb_pol = c->nb[2]; a.nc_pol = c->ncnt[2]; a.cap_pol = c->cap[2];
     a.nb_ipol = c->nb[3]; a.nc_ipol = c->ncnt[3]; a.cap_ipol = c->cap[3];
     a.cellmax = c->cellmax;
+    a.slices = nlist_slices(c->n, c->ncell);
     a.err = c->dints + 5;
     {
       Phase ph(c, SIBFA_PH_LISTS);
       launch_nlist(a, c->ncell, c->stream);
-      launch_cellmax_reduce(c->cellmax, c->ncell, c->dints, c->stream);
+      launch_cellmax_reduce(c->cellmax, c->ncell * a.slices, c->dints, c->stream);
     }
     if (attempt == 0) beside();
     HIP_TRY(hipMemcpyAsync(c->h_ints, c->dints, 8 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
@@ -703,9 +704,13 @@ sibfa_status prepare(sibfa_ctx c) {
     {
       Phase ph(c, SIBFA_PH_LISTS);
       launch_bin(b, s);
-      launch_exclusive_scan(c->cell_count, c->cell_start, c->ncell + 1, c->scan_tmp, s);
-      launch_scatter(c->cell_of, c->cell_start, c->cursor, c->perm, c->n, s);
-      launch_sort_cells(c->cell_start, c->ncell, c->perm, s);
+      if (c->periodic) {
+        launch_exclusive_scan(c->cell_count, c->cell_start, c->ncell + 1, c->scan_tmp, s);
+        launch_scatter(c->cell_of, c->cell_start, c->cursor, c->perm, c->n, s);
+        launch_sort_cells(c->cell_start, c->ncell, c->perm, s);
+      } else {
+        launch_one_cell(c->perm, c->cell_start, c->n, s);
+      }
       launch_rec_all(ra, s);
     }
     if (!c->ids_ok) {
@@ -1694,10 +1699,12 @@ size_t sibfa_footprint_bytes(int n_sites, int n_polarizable, const double* box,
       tiles *= (size_t)((p->grid[a] + e - 1) / e) * (e + p->order - 1);
     }
     bytes += tiles * (8 + 4);
-    size_t cells = 1;   // cell grid as in sibfa_set_system: count, start, cursor, maxima
+    // cell grid as in sibfa_set_system: count, start, cursor; list maxima
+    size_t cells = 1;
     for (int a = 0; a < 3; ++a)
       cells *= (size_t)std::max(1, std::min(1024, (int)std::floor(box[a] / (0.5 * p->cutoff))));
-    bytes += cells * (3 * sizeof(int) + sizeof(int4));
+    bytes += cells * 3 * sizeof(int) +
+             cells * (size_t)nlist_slices((int)n, (int)cells) * sizeof(int4);
   } else {
     cap_all = n;
     cap_pol = np;
@@ -1746,7 +1753,7 @@ sibfa_status sibfa_set_system(sibfa_ctx c, int n_sites, const double* xyz, const
             alloc_into(c, L, c->mu_c, 3 * n) && alloc_into(c, L, c->mol_c, n) &&
             alloc_into(c, L, c->cell_of, n) && alloc_into(c, L, c->cell_count, c->ncell + 1) &&
             alloc_into(c, L, c->cell_start, c->ncell + 1) && alloc_into(c, L, c->cursor, c->ncell) &&
-            alloc_into(c, L, c->cellmax, c->ncell) &&
+            alloc_into(c, L, c->cellmax, (size_t)c->ncell * nlist_slices(n_sites, c->ncell)) &&
             alloc_into(c, L, c->perm, n) && alloc_into(c, L, c->inv_perm, n) &&
             alloc_into(c, L, c->mol_count, n) && alloc_into(c, L, c->mol_s, n) &&
             alloc_into(c, L, c->scan_tmp, scan_temp_ints((int)std::max<size_t>(n + 1, c->ncell + 1)) + 16) &&

@@ -42,6 +42,7 @@ struct RecArgs {
 
 struct NlistArgs {
   int periodic;
+  int slices;            // wavefronts per cell (nlist_slices)
   int nc[3];
   double box[3], ibox[3];
   double cutoff2;
@@ -59,16 +60,18 @@ struct NlistArgs {
   int* nb_in; int* nc_in; int cap_in;
   int* nb_pol; int* nc_pol; int cap_pol;
   int* nb_ipol; int* nc_ipol; int cap_ipol;
-  // [cell] maxima of the four counts over the cell's sites, written by the
-  // cell's wavefront (no atomics: one same-address atomic per wavefront
+  // [cell * slices + slice] maxima of the four counts over the slice's
+  // sites, written by its wavefront (no atomics: one same-address atomic per wavefront
   // costs the launch more than the list build itself)
   int4* cellmax;
   int* err;              // bit 1: a molecule's sites not all within reach
 };
 
 void launch_bin(const BinArgs& a, hipStream_t s);
-// out[0..3] = the maxima of cellmax over ncell cells
-void launch_cellmax_reduce(const int4* cellmax, int ncell, int* out, hipStream_t s);
+// out[0..3] = the maxima of cellmax over its count entries
+void launch_cellmax_reduce(const int4* cellmax, int count, int* out, hipStream_t s);
+// One cell holding every site in caller order: perm[i] = i, cell_start = {0, n}.
+void launch_one_cell(int* perm, int* cell_start, int n, hipStream_t s);
 void launch_scatter(const int* cell_of, const int* cell_start, int* cursor, int* perm,
                     int n, hipStream_t s);
 void launch_sort_cells(const int* cell_start, int ncell, int* perm, hipStream_t s);
@@ -83,6 +86,11 @@ void launch_pol_extents(const RecArgs& a, double* out, hipStream_t s);
 void launch_rec_mult(const RecArgs& a, hipStream_t s);
 void launch_rec_pol(const RecArgs& a, hipStream_t s);
 void launch_rec_polsites(const RecArgs& a, hipStream_t s);
+// Wavefronts per cell of the list build: the builder is issue-bound once
+// about kNlWaves wavefronts share the 1,024 SIMDs and bound by one
+// wavefront's chain below that.
+constexpr int kNlWaves = 8192;
+int nlist_slices(int n, int ncell);
 void launch_nlist(const NlistArgs& a, int ncell, hipStream_t s);
 
 }  // namespace sibfa

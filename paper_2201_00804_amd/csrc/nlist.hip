@@ -4,10 +4,11 @@
 // Sites are binned into cells of edge >= cutoff/2 (a 5x5x5 cell stencil
 // then covers the cutoff sphere), counting-sorted by cell, and each cell's
 // segment is sorted by caller index so that the order -- and with it every
-// summation order downstream -- is reproducible.  The neighbour-list kernel
-// runs one wavefront per cell: 64 candidate sites are loaded per step and
-// tested against every site of the cell; hits are compacted with ballots so
-// list order is deterministic too.  Four ELL lists are produced:
+// summation order downstream -- is reproducible (a cluster is one cell, in
+// caller order).  The neighbour-list kernel runs one or more wavefronts per
+// cell: 64 candidate sites are loaded per step and tested against the
+// wavefront's sites; hits are compacted with lane masks so list order is
+// deterministic too.  Four ELL lists are produced:
 //   all   intermolecular site pairs within the cutoff (E, E_elec, forces)
 //   in    same-molecule site pairs (excluded or damped, always present)
 //   pol   intermolecular polarizable pairs within the cutoff (T)
@@ -265,6 +266,20 @@ __global__ __launch_bounds__(64) void k_sort_cells(const int* cell_start, int nc
   }
 }
 
+// Clusters: one cell in caller order, what the counting sort would give
+// (its one-cell segment is past the rank sort's LDS buffer from 257 sites
+// on: 5.9 ms for 400 sites, against 3 us here).
+__global__ void k_one_cell(int* perm, int* cell_start, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) perm[i] = i;
+  if (i == 0) { cell_start[0] = 0; cell_start[1] = n; }
+}
+
+void launch_one_cell(int* perm, int* cell_start, int n, hipStream_t s) {
+  hipLaunchKernelGGL(k_one_cell, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, perm,
+                     cell_start, n);
+}
+
 __global__ void k_sum_ints(const int* v, int n, unsigned long long* out) {
   unsigned long long m = 0;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
@@ -469,170 +484,34 @@ void launch_pol_extents(const RecArgs& a, double* out, hipStream_t s) {
 }
 
 // ------------------------------------------------------------ neighbour lists
-constexpr int kNlIB = 64;   // i-sites of a cell handled per pass (one per lane)
-
-// The running count of each list for i-site t lives in lane t (cnt_*), read
-// back wave-uniformly with readlane, so the inner loop needs neither LDS
-// counters nor barriers; the block is a single wavefront.
-__global__ __launch_bounds__(64) void k_nlist(NlistArgs a) {
-  __shared__ double xi[kNlIB], yi[kNlIB], zi[kNlIB];
-  __shared__ int moli[kNlIB], poli[kNlIB];
-  const int lane = threadIdx.x;
-  const int cell = blockIdx.x;
-  const int cx = cell % a.nc[0];
-  const int cy = (cell / a.nc[0]) % a.nc[1];
-  const int cz = cell / (a.nc[0] * a.nc[1]);
-  const int i0 = a.cell_start[cell], i1 = a.cell_start[cell + 1];
-  const double L0 = a.box[0], L1 = a.box[1], L2 = a.box[2];
-  const double iL0 = a.ibox[0], iL1 = a.ibox[1], iL2 = a.ibox[2];
-  const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  // stencil extents per axis: all cells when the axis has fewer than 5
-  int span[3], lo[3];
-  const int c3[3] = {cx, cy, cz};
-  for (int d = 0; d < 3; ++d) {
-    if (a.nc[d] < 5) { span[d] = a.nc[d]; lo[d] = 0; }
-    else { span[d] = 5; lo[d] = c3[d] - 2; }
-  }
-  int4 mx = make_int4(0, 0, 0, 0);   // the cell's count maxima
-  for (int ib = i0; ib < i1; ib += kNlIB) {
-    const int ni = min(kNlIB, i1 - ib);
-    if (lane < ni) {
-      const double4 p = a.sp[ib + lane];
-      xi[lane] = p.x; yi[lane] = p.y; zi[lane] = p.z;
-      moli[lane] = a.mol_s[ib + lane];
-      poli[lane] = a.polidx[ib + lane];
-    }
-    __syncthreads();
-    // counts of i-site `lane`: all near (cnt0) and far (cntf), in, pol, ipol
-    int cnt0 = 0, cntf = 0, cnt1 = 0, cnt2 = 0, cnt3 = 0;
-    for (int sz = 0; sz < span[2]; ++sz) {
-      int zz = lo[2] + sz;
-      zz = (zz + a.nc[2]) % a.nc[2];
-      for (int sy = 0; sy < span[1]; ++sy) {
-        int yy = lo[1] + sy;
-        yy = (yy + a.nc[1]) % a.nc[1];
-        const int rowcell = a.nc[0] * (yy + a.nc[1] * zz);
-        // x cells of this row as at most two contiguous runs
-        int rs[2], re[2], nrun;
-        if (span[0] == a.nc[0]) {
-          rs[0] = rowcell; re[0] = rowcell + a.nc[0]; nrun = 1;
-        } else {
-          const int x0 = lo[0], x1 = lo[0] + 4;
-          if (x0 >= 0 && x1 < a.nc[0]) { rs[0] = rowcell + x0; re[0] = rowcell + x1 + 1; nrun = 1; }
-          else if (x0 < 0) {
-            rs[0] = rowcell; re[0] = rowcell + x1 + 1;
-            rs[1] = rowcell + a.nc[0] + x0; re[1] = rowcell + a.nc[0]; nrun = 2;
-          } else {
-            rs[0] = rowcell + x0; re[0] = rowcell + a.nc[0];
-            rs[1] = rowcell; re[1] = rowcell + (x1 - a.nc[0]) + 1; nrun = 2;
-          }
-        }
-        for (int r = 0; r < nrun; ++r) {
-          const int j0 = a.cell_start[rs[r]], j1 = a.cell_start[re[r]];
-          for (int jc = j0; jc < j1; jc += 64) {
-            const int j = jc + lane;
-            const bool valid = j < j1;
-            double xj = 0, yj = 0, zj = 0;
-            int molj = -1, polj = -1;
-            if (valid) {
-              const double4 p = a.sp[j];
-              xj = p.x; yj = p.y; zj = p.z;
-              molj = a.mol_s[j];
-              polj = a.polidx[j];
-            }
-            for (int t = 0; t < ni; ++t) {
-              double dx = xi[t] - xj, dy = yi[t] - yj, dz = zi[t] - zj;
-              if (a.periodic) {
-                dx -= L0 * rint(dx * iL0);
-                dy -= L1 * rint(dy * iL1);
-                dz -= L2 * rint(dz * iL2);
-              }
-              const double r2 = dx * dx + dy * dy + dz * dz;
-              const int i = ib + t;
-              const int mi = moli[t], pi_ = poli[t];
-              const bool same = valid && (molj == mi) && (j != i);
-              const bool inter = valid && (molj != mi) && (r2 < a.cutoff2);
-              const bool near = r2 < a.rsplit2;
-              const bool pi = pi_ >= 0;
-              const bool pj = polj >= 0;
-              const unsigned long long b0 = __ballot(inter && near);
-              const unsigned long long bf = __ballot(inter && !near);
-              const unsigned long long b1 = __ballot(same);
-              const unsigned long long b2 = __ballot(inter && pi && pj);
-              const unsigned long long b3 = __ballot(same && pi && pj);
-              const int base0 = __shfl(cnt0, t, 64), basef = __shfl(cntf, t, 64);
-              const int base1 = __shfl(cnt1, t, 64);
-              const int base2 = __shfl(cnt2, t, 64), base3 = __shfl(cnt3, t, 64);
-              if (inter && near) {
-                const int k = base0 + __popcll(b0 & below);
-                if (k < a.cap_all) a.nb_all[(size_t)i * a.cap_all + k] = j;
-              }
-              if (inter && !near) {
-                const int k = basef + __popcll(bf & below);
-                if (k < a.cap_all) a.nb_all[(size_t)i * a.cap_all + a.cap_all - 1 - k] = j;
-              }
-              if (same) {
-                const int k = base1 + __popcll(b1 & below);
-                if (k < a.cap_in) a.nb_in[(size_t)i * a.cap_in + k] = j;
-              }
-              if (inter && pi && pj) {
-                const int k = base2 + __popcll(b2 & below);
-                if (k < a.cap_pol) a.nb_pol[(size_t)pi_ * a.cap_pol + k] = polj;
-              }
-              if (same && pi && pj) {
-                const int k = base3 + __popcll(b3 & below);
-                if (k < a.cap_ipol) a.nb_ipol[(size_t)pi_ * a.cap_ipol + k] = polj;
-              }
-              if (lane == t) {
-                cnt0 += __popcll(b0);
-                cntf += __popcll(bf);
-                cnt1 += __popcll(b1);
-                cnt2 += __popcll(b2);
-                cnt3 += __popcll(b3);
-              }
-            }
-          }
-        }
-      }
-    }
-    // counts, overflow maxima and the same-molecule completeness check
-    if (lane < ni) {
-      const int i = ib + lane;
-      a.nc_all[i] = cnt0 + cntf;
-      a.nc_near[i] = cnt0;
-      a.nc_in[i] = cnt1;
-      if (poli[lane] >= 0) {
-        a.nc_pol[poli[lane]] = cnt2;
-        a.nc_ipol[poli[lane]] = cnt3;
-      }
-      if (cnt1 != a.mol_count[moli[lane]] - 1) atomicOr(a.err, 1);
-    }
-    mx.x = max(mx.x, wave_max(lane < ni ? cnt0 + cntf : 0));
-    mx.y = max(mx.y, wave_max(lane < ni ? cnt1 : 0));
-    mx.z = max(mx.z, wave_max(lane < ni && poli[lane] >= 0 ? cnt2 : 0));
-    mx.w = max(mx.w, wave_max(lane < ni && poli[lane] >= 0 ? cnt3 : 0));
-    __syncthreads();
-  }
-  if (lane == 0) a.cellmax[cell] = mx;
-}
-
-// Periodic boxes with at least five cells along every axis.  Same lists, in
-// the same order, as k_nlist, with changes that cut the work per candidate
-// pair:
+// One wavefront builds the rows of one slice of a cell's sites: the cell's
+// sites are dealt to `slices` wavefronts in contiguous runs (launch_nlist's
+// caller picks the count, nlist_slices), and lists and their order do not
+// depend on it.  Bound by vector issue where the wavefronts fill the SIMDs
+// (0.42 of the issue peak at 32,000 waters) and by the length of one
+// wavefront's chain of candidate chunks where they do not: with one
+// wavefront per cell the build took 300 us at 4,096 waters, 770 us at 1,001
+// and 1.3 ms for a cluster of 80 (one cell), and whole evaluations went
+// 1.98 -> 1.81, 2.70 -> 2.02 and (with k_one_cell) 4.59 -> 0.47 ms.
 //  * the 5 x 5 rows of the stencil give at most 50 runs of consecutive
 //    cells, each with a fixed periodic image shift (the stencil reaches a
 //    wrapped cell through exactly one image), so a candidate's displacement
-//    is x_i - (x_j + shift) without a per-pair rint;
+//    is x_i - (x_j + shift) without a per-pair rint.  Along an axis of fewer
+//    than five cells every cell is a candidate once and the displacement is
+//    brought to the nearest image per pair instead (NI); a cluster is one
+//    cell without images;
 //  * the runs are concatenated into one virtual candidate range, taken
 //    kNlG chunks of 64 at a time into registers (a lane finds its run by
 //    binary search over the run offsets), so chunks are full;
-//  * each i-site's five running counts are read once per pass over those
-//    chunks into wave-uniform (scalar) registers, so a candidate chunk costs
-//    the distance test, the lane masks and the slot arithmetic of its hits;
-//  * the cell's count maxima go to its own slot of cellmax (plain stores;
+//  * each i-site's five running counts live in lane t and are read once per
+//    pass over those chunks into wave-uniform (scalar) registers, so a
+//    candidate chunk costs the distance test, the lane masks and the slot
+//    arithmetic of its hits; hits are compacted in lane order;
+//  * the slice's count maxima go to its own slot of cellmax (plain stores;
 //    launch_cellmax_reduce folds them), not to one atomic per wavefront on
 //    four shared addresses.
-constexpr int kNlG = 4;   // candidate chunks per pass over the i-sites
+constexpr int kNlIB = 64;   // i-sites handled per pass (one per lane)
+constexpr int kNlG = 4;     // candidate chunks per pass over the i-sites
 
 __device__ __forceinline__ int rl(int v, int t) { return __builtin_amdgcn_readlane(v, t); }
 // lane masks straight from one vector compare (predicate codes of the
@@ -645,50 +524,79 @@ __device__ __forceinline__ unsigned long long mask_eq(int a, int b) {
   return __builtin_amdgcn_sicmp(a, b, kCmpEQ);
 }
 
-__global__ __launch_bounds__(64) void k_nlist_shift(NlistArgs a) {
+template <bool NI>
+__global__ __launch_bounds__(64) void k_nlist(NlistArgs a) {
   __shared__ double xi[kNlIB], yi[kNlIB], zi[kNlIB];
   __shared__ int run_s[50], run_off[51], run_code[50];
   const int lane = threadIdx.x;
-  const int cell = blockIdx.x;
+  const int cell = blockIdx.x / a.slices, slice = blockIdx.x - cell * a.slices;
   const int nc0 = a.nc[0], nc1 = a.nc[1], nc2 = a.nc[2];
   const int cx = cell % nc0, cy = (cell / nc0) % nc1, cz = cell / (nc0 * nc1);
-  const int i0 = a.cell_start[cell], i1 = a.cell_start[cell + 1];
+  const int c0 = a.cell_start[cell], c1 = a.cell_start[cell + 1];
+  const int per = (c1 - c0 + a.slices - 1) / a.slices;
+  const int i0 = min(c1, c0 + slice * per), i1 = min(c1, i0 + per);
+  if (i0 >= i1) {
+    if (lane == 0) a.cellmax[blockIdx.x] = make_int4(0, 0, 0, 0);
+    return;
+  }
   const double L0 = a.box[0], L1 = a.box[1], L2 = a.box[2];
-  if (lane < 25) {
-    const int dz = lane / 5 - 2, dy = lane % 5 - 2;
-    int zz = cz + dz, zc = 1;
-    if (zz < 0) { zz += nc2; zc = 0; } else if (zz >= nc2) { zz -= nc2; zc = 2; }
-    int yy = cy + dy, yc = 1;
-    if (yy < 0) { yy += nc1; yc = 0; } else if (yy >= nc1) { yy -= nc1; yc = 2; }
+  // axes taken whole, and the box edges their displacements wrap by (0: no
+  // wrap along this axis)
+  const bool w0 = nc0 < 5, w1 = nc1 < 5, w2 = nc2 < 5;
+  const double W0 = NI && w0 ? L0 : 0.0, W1 = NI && w1 ? L1 : 0.0, W2 = NI && w2 ? L2 : 0.0;
+  const double iW0 = NI && w0 ? a.ibox[0] : 0.0, iW1 = NI && w1 ? a.ibox[1] : 0.0,
+               iW2 = NI && w2 ? a.ibox[2] : 0.0;
+  const int sy = w1 ? nc1 : 5, sz = w2 ? nc2 : 5;
+  int len0 = 0, len1 = 0;   // lengths of this lane's two runs
+  if (lane < sy * sz) {
+    int zz, yy, zc = 1, yc = 1;   // image codes: 0 below, 1 home, 2 above
+    if (w2) zz = lane / sy;
+    else {
+      zz = cz + lane / sy - 2;
+      if (zz < 0) { zz += nc2; zc = 0; } else if (zz >= nc2) { zz -= nc2; zc = 2; }
+    }
+    if (w1) yy = lane % sy;
+    else {
+      yy = cy + lane % sy - 2;
+      if (yy < 0) { yy += nc1; yc = 0; } else if (yy >= nc1) { yy -= nc1; yc = 2; }
+    }
     const int row = nc0 * (yy + nc1 * zz);
     const int x0 = cx - 2, x1 = cx + 2;
-    int f0, l0, c0, f1 = 0, l1 = -1, c1 = 1;   // cell ranges [f, l] and x image codes
-    if (x0 >= 0 && x1 < nc0) { f0 = x0; l0 = x1; c0 = 1; }
-    else if (x0 < 0) { f0 = 0; l0 = x1; c0 = 1; f1 = nc0 + x0; l1 = nc0 - 1; c1 = 0; }
-    else { f0 = x0; l0 = nc0 - 1; c0 = 1; f1 = 0; l1 = x1 - nc0; c1 = 2; }
+    int f0, l0, k0, f1 = 0, l1 = -1, k1 = 1;   // cell ranges [f, l] and x image codes
+    if (w0) { f0 = 0; l0 = nc0 - 1; k0 = 1; }
+    else if (x0 >= 0 && x1 < nc0) { f0 = x0; l0 = x1; k0 = 1; }
+    else if (x0 < 0) { f0 = 0; l0 = x1; k0 = 1; f1 = nc0 + x0; l1 = nc0 - 1; k1 = 0; }
+    else { f0 = x0; l0 = nc0 - 1; k0 = 1; f1 = 0; l1 = x1 - nc0; k1 = 2; }
     const int yzc = 3 * yc + 9 * zc;
     run_s[2 * lane] = a.cell_start[row + f0];
-    run_off[2 * lane + 1] = a.cell_start[row + l0 + 1] - a.cell_start[row + f0];
-    run_code[2 * lane] = c0 + yzc;
+    len0 = a.cell_start[row + l0 + 1] - a.cell_start[row + f0];
+    run_code[2 * lane] = k0 + yzc;
     if (l1 >= f1) {
       run_s[2 * lane + 1] = a.cell_start[row + f1];
-      run_off[2 * lane + 2] = a.cell_start[row + l1 + 1] - a.cell_start[row + f1];
+      len1 = a.cell_start[row + l1 + 1] - a.cell_start[row + f1];
     } else {
       run_s[2 * lane + 1] = 0;
-      run_off[2 * lane + 2] = 0;
     }
-    run_code[2 * lane + 1] = c1 + yzc;
+    run_code[2 * lane + 1] = k1 + yzc;
+  }
+  {
+    int x = len0 + len1;   // inclusive scan over the rows
+    for (int off = 1; off < 32; off <<= 1) {
+      const int y = __shfl_up(x, off, 64);
+      if (lane >= off) x += y;
+    }
+    if (lane < 25) {
+      run_off[2 * lane + 1] = x - len1;
+      run_off[2 * lane + 2] = x;
+    }
+    if (lane == 0) run_off[0] = 0;
   }
   __syncthreads();
-  if (lane == 0) {
-    run_off[0] = 0;
-    for (int r = 1; r <= 50; ++r) run_off[r] += run_off[r - 1];
-  }
-  __syncthreads();
-  const int ncand = run_off[50];
-  const int cap_all = a.cap_all, cap_in = a.cap_in, cap_pol = a.cap_pol, cap_ipol = a.cap_ipol;
+  const int ncand = run_off[50], nrun = 2 * sy * sz;
+  const unsigned cap_all = a.cap_all;
+  const int cap_in = a.cap_in, cap_pol = a.cap_pol, cap_ipol = a.cap_ipol;
   const double cut2 = a.cutoff2, split2 = a.rsplit2;
-  int4 mx = make_int4(0, 0, 0, 0);   // the cell's count maxima
+  int4 mx = make_int4(0, 0, 0, 0);   // the slice's count maxima
   for (int ib = i0; ib < i1; ib += kNlIB) {
     const int ni = min(kNlIB, i1 - ib);
     // i-site `lane`: position in LDS (read back as a broadcast), molecule
@@ -704,18 +612,18 @@ __global__ __launch_bounds__(64) void k_nlist_shift(NlistArgs a) {
     // counts of i-site `lane`: all near (cnt0) and far (cntf), in, pol, ipol
     int cnt0 = 0, cntf = 0, cnt1 = 0, cnt2 = 0, cnt3 = 0;
     for (int c = 0; c < ncand; c += 64 * kNlG) {
-      // a lane past the candidates sits far away in no molecule: it never
-      // tests as a neighbour
+      // a lane past the candidates sits at infinity in no molecule: it
+      // never tests as a neighbour (also of a cluster's infinite cutoff)
       double xj[kNlG], yj[kNlG], zj[kNlG];
       int jj[kNlG], molj[kNlG], polj[kNlG];
       unsigned long long pjm[kNlG];
 #pragma unroll
       for (int g = 0; g < kNlG; ++g) {
         const int cidx = c + g * 64 + lane;
-        xj[g] = yj[g] = zj[g] = 1e30;
+        xj[g] = yj[g] = zj[g] = INFINITY;
         jj[g] = -1; molj[g] = -1; polj[g] = -1;
         if (cidx < ncand) {
-          int lo = 0, hi = 50;
+          int lo = 0, hi = nrun;
           while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
             if (run_off[mid] <= cidx) lo = mid; else hi = mid;
@@ -746,7 +654,12 @@ __global__ __launch_bounds__(64) void k_nlist_shift(NlistArgs a) {
         int* row_ipol = a.nb_ipol + (size_t)(pi_ >= 0 ? pi_ : 0) * cap_ipol;
 #pragma unroll
         for (int g = 0; g < kNlG; ++g) {
-          const double dx = x - xj[g], dy = y - yj[g], dz = z - zj[g];
+          double dx = x - xj[g], dy = y - yj[g], dz = z - zj[g];
+          if (NI) {
+            dx -= W0 * rint(dx * iW0);
+            dy -= W1 * rint(dy * iW1);
+            dz -= W2 * rint(dz * iW2);
+          }
           const double r2 = dx * dx + dy * dy + dz * dz;
           // the same compares give the wave's masks and each lane's own
           // bit (the compiler folds them into one instruction each)
@@ -759,22 +672,17 @@ __global__ __launch_bounds__(64) void k_nlist_shift(NlistArgs a) {
           unsigned long long b1 = 0ull;        // same molecule, not site t itself
           if (bmol) b1 = bmol & ~mask_eq(jj[g], i);
           if (b0) {
+            // near entries from the front of the row, far ones from its
+            // back, in one store
             const unsigned long long bnear = mask_lt(r2, split2);
             const unsigned long long bn = b0 & bnear, bf = b0 & ~bnear;
-            if (bn) {
-              if (inter && in_near) {
-                const int k = lanes_below(bn, k0);
-                if (k < cap_all) row_all[(unsigned)k] = jj[g];
-              }
-              k0 += __popcll(bn);
+            if (inter) {
+              const int kn = lanes_below(bn, k0), kb = lanes_below(bf, kf);
+              const unsigned k = in_near ? (unsigned)kn : cap_all - 1u - (unsigned)kb;
+              if (k < cap_all) row_all[k] = jj[g];
             }
-            if (bf) {
-              if (inter && !in_near) {
-                const int k = lanes_below(bf, kf);
-                if (k < cap_all) row_all[(unsigned)(cap_all - 1 - k)] = jj[g];
-              }
-              kf += __popcll(bf);
-            }
+            k0 += __popcll(bn);
+            kf += __popcll(bf);
           }
           if (b1) {
             if (same) {
@@ -823,13 +731,13 @@ __global__ __launch_bounds__(64) void k_nlist_shift(NlistArgs a) {
     mx.w = max(mx.w, wave_max(pol_v >= 0 ? cnt3 : 0));
     __syncthreads();
   }
-  if (lane == 0) a.cellmax[cell] = mx;
+  if (lane == 0) a.cellmax[blockIdx.x] = mx;
 }
 
-__global__ __launch_bounds__(1024) void k_cellmax_reduce(const int4* cellmax, int ncell, int* out) {
+__global__ __launch_bounds__(1024) void k_cellmax_reduce(const int4* cellmax, int count, int* out) {
   __shared__ int4 part[16];
   int4 m = make_int4(0, 0, 0, 0);
-  for (int k = threadIdx.x; k < ncell; k += blockDim.x) {
+  for (int k = threadIdx.x; k < count; k += blockDim.x) {
     const int4 v = cellmax[k];
     m.x = max(m.x, v.x); m.y = max(m.y, v.y); m.z = max(m.z, v.z); m.w = max(m.w, v.w);
   }
@@ -847,15 +755,24 @@ __global__ __launch_bounds__(1024) void k_cellmax_reduce(const int4* cellmax, in
   }
 }
 
-void launch_cellmax_reduce(const int4* cellmax, int ncell, int* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_cellmax_reduce, dim3(1), dim3(1024), 0, s, cellmax, ncell, out);
+void launch_cellmax_reduce(const int4* cellmax, int count, int* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_cellmax_reduce, dim3(1), dim3(1024), 0, s, cellmax, count, out);
+}
+
+// Wavefronts per cell: enough for kNlWaves in all, at most one per site of
+// an average cell.
+int nlist_slices(int n, int ncell) {
+  const int per_cell = (n + ncell - 1) / ncell;
+  return std::max(1, std::min(per_cell, kNlWaves / ncell));
 }
 
 void launch_nlist(const NlistArgs& a, int ncell, hipStream_t s) {
-  if (a.periodic && a.nc[0] >= 5 && a.nc[1] >= 5 && a.nc[2] >= 5)
-    hipLaunchKernelGGL(k_nlist_shift, dim3(ncell), dim3(64), 0, s, a);
+  const dim3 g((unsigned)ncell * a.slices), b(64);
+  // a cluster needs no images; one that is periodic along a short axis does
+  if (a.periodic && (a.nc[0] < 5 || a.nc[1] < 5 || a.nc[2] < 5))
+    hipLaunchKernelGGL(k_nlist<true>, g, b, 0, s, a);
   else
-    hipLaunchKernelGGL(k_nlist, dim3(ncell), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_nlist<false>, g, b, 0, s, a);
 }
 
 }  // namespace sibfa
