@@ -485,10 +485,10 @@ sibfa_status sibfa_batch_clusters(sibfa_batch b, int n_clusters,
  * For callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  The same
  * computation and kernels as sibfa_batch_clusters, with no executor: the
- * scratch arrays live in a fixed device array of the library (about 8 MB,
+ * scratch arrays live in a fixed device array of the library (about 6 MB,
  * for at most SIBFA_BATCH_NOALLOC_MAX_SITES sites and
  * SIBFA_BATCH_NOALLOC_MAX_CLUSTERS clusters per call), which each device
- * holds until the process ends.  The call allocates nothing, enqueues three
+ * holds until the process ends.  The call allocates nothing, enqueues its
  * kernels on hip_stream (a hipStream_t; NULL = null stream) on `device` and
  * returns; it neither synchronises nor copies from the host.
  *

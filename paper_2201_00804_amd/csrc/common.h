@@ -256,9 +256,30 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+// v of the lane n places lower in this lane's row of 16 (cyclic): a register
+// move, where a general shuffle is a trip through LDS (about 60 cycles, two
+// per double).
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// Sum over each row of 16 lanes, in every lane: the order (and so the bits)
+// of the butterfly v += v[lane ^ 8], 4, 2, 1.
+__device__ __forceinline__ double row_sum(double v) {
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
   return v;
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+  v += __shfl_xor(v, 32, 64);
+  v += __shfl_xor(v, 16, 64);
+  return row_sum(v);
 }
 
 __device__ __forceinline__ int wave_max(int v) {
@@ -269,6 +290,7 @@ __device__ __forceinline__ int wave_max(int v) {
 // Sum over groups of G consecutive lanes (G a power of two <= 64).
 template <int G>
 __device__ __forceinline__ double group_sum(double v) {
+  if (G == 16) return row_sum(v);
   for (int off = G / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, G);
   return v;
 }
