@@ -1463,16 +1463,36 @@ sibfa_status tcg_forces(sibfa_ctx c, int n, double omega, bool warm, double* e_p
   return SIBFA_OK;
 }
 
-// Spreading brick edge along an axis of K points: the largest size <=
-// kBrick whose last (partial) brick still spans order - 1 points, so that
-// every grid point lies in the tiles of at most two bricks per axis; 0 if
-// none fits.
-int brick_edge(int K, int order) {
-  for (int b = kBrick; b >= order - 1 && b >= 1; --b) {
+// Spreading brick edge along an axis of K points: the largest size <= most
+// whose last (partial) brick still spans order - 1 points, so that every
+// grid point lies in the tiles of at most two bricks per axis; 0 if none
+// fits.
+int brick_edge(int K, int order, int most) {
+  for (int b = most; b >= order - 1 && b >= 1; --b) {
     const int rem = K % b;
     if (rem == 0 || rem >= order - 1) return b;
   }
   return 0;
+}
+
+// Brick edges of a grid (0 where none fits).  Edges of up to kBrick points
+// unless that leaves bricks for fewer workgroups than the GPU has CUs and
+// the context is FP64: then of kBrickSmall where the grid allows it, since
+// one workgroup adds its brick's sites one after the other (up to 81 sites
+// in a brick of 8^3 points, 24 in one of 4^3).  A mixed context keeps the
+// larger bricks: its FP32 tile sums would round differently.
+constexpr int kBrickSmall = 4, kBrickFew = 256;
+void brick_edges(const sibfa_params& p, int edge[3]) {
+  int bricks = 1;
+  for (int a = 0; a < 3; ++a) {
+    edge[a] = brick_edge(p.grid[a], p.order, kBrick);
+    bricks *= edge[a] ? (p.grid[a] + edge[a] - 1) / edge[a] : 1;
+  }
+  if (p.precision != SIBFA_FP64 || bricks > kBrickFew) return;
+  for (int a = 0; a < 3; ++a) {
+    const int e = brick_edge(p.grid[a], p.order, kBrickSmall);
+    if (e) edge[a] = e;
+  }
 }
 
 sibfa_status setup_pme(sibfa_ctx c) {
@@ -1495,8 +1515,8 @@ sibfa_status setup_pme(sibfa_ctx c) {
   }
   pm.kxh = pm.K[0] / 2 + 1;
   pm.beta = c->prm.ewald_beta;
+  brick_edges(c->prm, pm.Bb);
   for (int a = 0; a < 3; ++a) {
-    pm.Bb[a] = brick_edge(pm.K[a], order);
     if (pm.Bb[a] == 0) return fail(c, SIBFA_E_ARG, "no spreading brick size fits this grid");
     pm.nb[a] = (pm.K[a] + pm.Bb[a] - 1) / pm.Bb[a];
   }
@@ -1694,8 +1714,10 @@ size_t sibfa_footprint_bytes(int n_sites, int n_polarizable, const double* box,
     const size_t nh = (size_t)(p->grid[0] / 2 + 1) * p->grid[1] * p->grid[2];
     bytes += nr * 2 * (8 + 4) + nh * (16 + 8 + 8 + 4);
     size_t tiles = 1;
+    int edge[3];
+    brick_edges(*p, edge);
     for (int a = 0; a < 3; ++a) {
-      const int e = std::max(brick_edge(p->grid[a], p->order), 1);
+      const int e = std::max(edge[a], 1);
       tiles *= (size_t)((p->grid[a] + e - 1) / e) * (e + p->order - 1);
     }
     bytes += tiles * (8 + 4);
@@ -1782,8 +1804,10 @@ sibfa_status sibfa_set_system(sibfa_ctx c, int n_sites, const double* xyz, const
   if (c->periodic) {
     mb += (size_t)c->prm.grid[1] * (c->prm.grid[0] / 2 + 1);
     size_t bricks = 1;
+    int edge[3];
+    brick_edges(c->prm, edge);
     for (int a = 0; a < 3; ++a) {
-      const int e = std::max(brick_edge(c->prm.grid[a], c->prm.order), 1);
+      const int e = std::max(edge[a], 1);
       bricks *= (size_t)((c->prm.grid[a] + e - 1) / e);
     }
     mb = std::max(mb, bricks);

@@ -82,132 +82,218 @@ __device__ __forceinline__ double* tile_buf<double>(const PmeView& pm) { return 
 template <>
 __device__ __forceinline__ float* tile_buf<float>(const PmeView& pm) { return pm.tiles32; }
 
+// B-spline weights of order P at offset w (derivatives up to ND <= 2) with
+// every rounding written out (explicit fused multiply-adds, contraction
+// off), so that the FP32 grid keeps its bits whatever code surrounds this:
+// the recursion of bspline_weights, a first derivative fused with the
+// scaling of its level.
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+template <typename R, int P, int ND>
+__device__ __forceinline__ void spread_weights(R w, R th[ND + 1][P]) {
+#pragma clang fp contract(off)
+  R lev[P][P], num[P][P];   // lev[k][t] = num / k = M_{k+1}(w + t)
+  lev[0][0] = R(1);
+#pragma unroll
+  for (int t = 1; t < P; ++t) lev[0][t] = R(0);
+#pragma unroll
+  for (int k = 1; k < P; ++k) {
+    const R inv = R(1) / R(k);
+#pragma unroll
+    for (int t = P - 1; t >= 0; --t) {
+      const R u = w + R(t);
+      const R a = t <= k - 1 ? lev[k - 1][t] : R(0);
+      const R b = t >= 1 && t - 1 <= k - 1 ? lev[k - 1][t - 1] : R(0);
+      num[k][t] = fma_(u, a, (R(k + 1) - u) * b);
+      lev[k][t] = num[k][t] * inv;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < P; ++t) {
+    th[0][t] = lev[P - 1][t];
+    if (ND >= 1)
+      th[ND >= 1 ? 1 : 0][t] =
+          t == 0 ? lev[P - 2][0] : fma_(R(1) / R(P - 2), num[P - 2][t], -lev[P - 2][t - 1]);
+    if (ND >= 2) {
+      const R b = t >= 1 ? lev[P - 3][t - 1] : R(0), c = t >= 2 ? lev[P - 3][t - 2] : R(0);
+      th[ND >= 2 ? 2 : 0][t] = fma_(b, R(-2), lev[P - 3][t]) + c;
+    }
+  }
+}
+
 // FULL: multipoles (q, d [+ mu], Theta) of all sites; otherwise the dipoles
 // of the polarizable sites.
 //
-// Owner-computes, no atomics: thread (x, y) of the workgroup owns one tile
-// column and keeps its T2 values in registers.  A site's contribution is a
-// sum of separable terms  A theta_x^(kx)(x) theta_y^(ky)(y) theta_z^(kz)(z),
-// regrouped by kz as  sum_kz U_kz(x, y) theta_z^(kz)(z).  Sites are staged
-// in chunks with their B-spline weights expanded to the tile width (zeros
-// outside the p-point support), so the inner loop is a few LDS reads (the z
-// weights are the same address for every lane) and FMAs.  The brick lists
-// are sorted by site index when they are built, so the tile sums -- and the
-// grid -- are reproducible bit for bit.
-constexpr int kSpreadBlock = 192;      // >= (kBrick + p - 1)^2 columns, p <= 6
+// One workgroup of two waves per brick, the tile in LDS.  The second wave
+// stages the brick's sites in chunks (amplitudes, and the P weights and
+// their derivatives per axis, three lanes per site); meanwhile the first
+// walks the chunk before, site by site in order, and adds each site's p^3
+// points to the tile, one point per lane (two rounds at p = 5): a read, the
+// three-axis product and a write per point, no atomics (a wave's LDS
+// accesses are in order).  Bound by instruction issue of the first wave,
+// about 36 per site and one every five cycles.  A thread per tile column
+// instead, its z values in registers, spent 5% of its multiply-adds on
+// points inside the site's support and 70 instructions of three waves per
+// site; splitting the tile's planes over four waves leaves each of them
+// most of the sites.  Dipole spread, thread per column -> this: 28 -> 16 us
+// at 4,096 waters (FP32), 81 -> 40 us at 32,000 (FP64, beside the matvec);
+// all multipoles 53 -> 32 us at 216 waters.
+// The brick lists are sorted by site index when they are built and one wave
+// adds them in that order, so the tile sums -- and the grid -- are
+// reproducible bit for bit.
+constexpr int kSpreadChunk = 21;   // sites per chunk: three lanes each of one wave
 
 template <bool FULL>
 struct SpreadShape {
-  static constexpr int ND = FULL ? 2 : 1;   // highest derivative order
-  static constexpr int NA = FULL ? 10 : 3;  // amplitudes per site
-  static constexpr int CH = FULL ? 32 : 64; // sites per staged chunk
+  static constexpr int ND = FULL ? 2 : 1;    // highest derivative order
+  static constexpr int NK = FULL ? 4 : 2;    // weights kept per point and axis (padded)
+  static constexpr int NA = FULL ? 12 : 4;   // amplitudes per site (padded)
 };
 
 template <typename R, int P, bool FULL>
-__global__ __launch_bounds__(kSpreadBlock) void k_spread_tile(SysView s, PmeView pm,
-                                                              const double4* vec) {
+struct SpreadChunk {
+  using Sh = SpreadShape<FULL>;
+  R wt[kSpreadChunk][3][P][Sh::NK];
+  R amp[kSpreadChunk][Sh::NA];
+  int top[kSpreadChunk];   // tile index of the site's highest point
+};
+
+// Site j of a chunk by the lane 3 j + ax of axis ax: idx its index, o the
+// axis' brick origin, T0 and T1 the tile's extents.
+template <typename R, int P, bool FULL>
+__device__ __forceinline__ void stage_site(const SysView& s, const PmeView& pm, const double4* vec,
+                                           SpreadChunk<R, P, FULL>& c, int j, int ax, int idx,
+                                           int o, int T0, int T1) {
+#pragma clang fp contract(off)
+  using Sh = SpreadShape<FULL>;
+  constexpr int ND = Sh::ND, NA = Sh::NA;
+  const double4 p = FULL ? s.sp[idx] : s.pp[idx];
+  const double xa = ax == 0 ? p.x : (ax == 1 ? p.y : p.z);
+  double fr;
+  const int base = grid_base(xa, pm.scale[ax], pm.K[ax], &fr);
+  R th[ND + 1][P];
+  spread_weights<R, P, ND>((R)fr, th);
+  const int top = base - o + P - 1;
+  const int ty = __shfl(top, 3 * j + 1, 64), tz = __shfl(top, 3 * j + 2, 64);
+#pragma unroll
+  for (int t = 0; t < P; ++t)
+#pragma unroll
+    for (int k = 0; k <= ND; ++k) c.wt[j][ax][t][k] = th[k][t];
+  if (ax != 0) return;
+  c.top[j] = (tz * T1 + ty) * T0 + top;
+  const R sc[3] = {(R)pm.scale[0], (R)pm.scale[1], (R)pm.scale[2]};
+  R* A = c.amp[j];
+  if (FULL) {
+    const double4 d4 = s.sd[idx], t4 = s.sth[idx];
+    const double2 t2 = s.sth2[idx];
+    double ddx = d4.x, ddy = d4.y, ddz = d4.z;
+    if (vec) {
+      const double4 m = vec[idx];
+      ddx += m.x; ddy += m.y; ddz += m.z;
+    }
+    const R third = R(1.0 / 3.0);
+    A[0] = (R)p.w;
+    A[1] = (R)ddx * sc[0];
+    A[2] = (R)ddy * sc[1];
+    A[3] = (R)ddz * sc[2];
+    A[4 % NA] = (R)t4.x * sc[0] * sc[0] * third;
+    A[5 % NA] = (R)t4.w * sc[1] * sc[1] * third;
+    A[6 % NA] = (R)t2.y * sc[2] * sc[2] * third;
+    A[7 % NA] = R(2) * third * (R)t4.y * sc[0] * sc[1];
+    A[8 % NA] = R(2) * third * (R)t4.z * sc[0] * sc[2];
+    A[9 % NA] = R(2) * third * (R)t2.x * sc[1] * sc[2];
+  } else {
+    const double4 pv = vec[idx];
+    A[0] = (R)pv.x * sc[0];
+    A[1] = (R)pv.y * sc[1];
+    A[2] = (R)pv.z * sc[2];
+  }
+}
+
+template <typename R, int P, bool FULL>
+__global__ __launch_bounds__(128) void k_spread_tile(SysView s, PmeView pm, const double4* vec) {
+#pragma clang fp contract(off)
   if (stopped(pm.stop)) return;
   using Sh = SpreadShape<FULL>;
-  constexpr int ND = Sh::ND, NA = Sh::NA, CH = Sh::CH;
-  constexpr int TM = kBrick + P - 1;
-  __shared__ R w[3][ND + 1][CH][TM];
-  __shared__ R amp[NA][CH];
-  const int tid = threadIdx.x;
-  const int T0 = pm.Bb[0] + P - 1, T1 = pm.Bb[1] + P - 1, T2 = pm.Bb[2] + P - 1;
-  const int nb0 = pm.nb[0], nb1 = pm.nb[1];
+  constexpr int NK = Sh::NK, NA = Sh::NA, CH = kSpreadChunk;
+  constexpr int TM = kBrick + P - 1, P3 = P * P * P, NR = (P3 + 63) / 64;
+  __shared__ __align__(16) R tile[TM * TM * TM];
+  __shared__ __align__(16) SpreadChunk<R, P, FULL> chunk[2];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const bool stager = tid >= 64;
   const int b = blockIdx.x;
-  const int o[3] = {(b % nb0) * pm.Bb[0], ((b / nb0) % nb1) * pm.Bb[1], (b / (nb0 * nb1)) * pm.Bb[2]};
   const int* start = FULL ? pm.bstart_all : pm.bstart_pol;
   const int* order = FULL ? pm.border_all : pm.border_pol;
   const int s0 = start[b], total = start[b + 1] - s0;
-  const bool owner = tid < T0 * T1;
-  const int cx = owner ? tid % T0 : 0, cy = owner ? tid / T0 : 0;
-  R acc[TM];
+  const int T0 = pm.Bb[0] + P - 1, T1 = pm.Bb[1] + P - 1, T2 = pm.Bb[2] + P - 1;
+  const int nb0 = pm.nb[0], nb1 = pm.nb[1], size = T0 * T1 * T2;
+  // the stager's site and axis; the spreader's points: offsets from a site's
+  // highest one and places of their weights (a lane past the support repeats
+  // the last point: the same value written twice)
+  const int sj = lane / 3, ax = lane - 3 * sj;
+  const int o = ax == 0 ? (b % nb0) * pm.Bb[0]
+                        : ax == 1 ? ((b / nb0) % nb1) * pm.Bb[1] : (b / (nb0 * nb1)) * pm.Bb[2];
+  int dx[NR], dy[NR], dz[NR], off[NR];
 #pragma unroll
-  for (int z = 0; z < TM; ++z) acc[z] = R(0);
-  const R sc[3] = {(R)pm.scale[0], (R)pm.scale[1], (R)pm.scale[2]};
-  for (int c0 = 0; c0 < total; c0 += CH) {
+  for (int r = 0; r < NR; ++r) {
+    const int q = min(lane + 64 * r, P3 - 1);
+    dx[r] = q % P;
+    dy[r] = q / P % P;
+    dz[r] = q / (P * P);
+    off[r] = (dz[r] * T1 + dy[r]) * T0 + dx[r];
+  }
+  if (stager) {
+    if (sj < min(CH, total))
+      stage_site<R, P, FULL>(s, pm, vec, chunk[0], sj, ax, order[s0 + sj], o, T0, T1);
+  } else {
+    for (int i = lane; i < size; i += 64) tile[i] = R(0);
+  }
+  int buf = 0;
+  for (int c0 = 0; c0 < total; c0 += CH, buf ^= 1) {
+    __syncthreads();   // chunk `buf` is staged, the other one is spread
     const int n = min(CH, total - c0);
-    __syncthreads();
-    if (tid < 3 * n) {
-      const int j = tid / 3, ax = tid - 3 * j;
-      const int idx = order[s0 + c0 + j];
-      const double4 p = FULL ? s.sp[idx] : s.pp[idx];
-      const double xa = ax == 0 ? p.x : (ax == 1 ? p.y : p.z);
-      double fr;
-      const int base = grid_base(xa, pm.scale[ax], pm.K[ax], &fr);
-      R th[ND + 1][P];
-      bspline_weights<R, P, ND>((R)fr, th);
-      const int top = base - o[ax] + P - 1;
+    if (stager) {
+      const int e = c0 + CH + sj;
+      if (sj < CH && e < total)
+        stage_site<R, P, FULL>(s, pm, vec, chunk[buf ^ 1], sj, ax, order[s0 + e], o, T0,
+                               T1);
+      continue;
+    }
+    const SpreadChunk<R, P, FULL>& c = chunk[buf];
+#pragma unroll 2
+    for (int j = 0; j < n; ++j) {
+      const R* A = c.amp[j];
+      const int base = c.top[j];
+      R v[NR];
 #pragma unroll
-      for (int k = 0; k <= ND; ++k)
-#pragma unroll
-        for (int z = 0; z < TM; ++z) {
-          const int d = top - z;
-          R v = R(0);
-#pragma unroll
-          for (int t = 0; t < P; ++t) v = d == t ? th[k][t] : v;
-          w[ax][k][j][z] = v;
-        }
-      if (ax == 0) {
+      for (int r = 0; r < NR; ++r) {
+        const R* X = c.wt[j][0][dx[r]];
+        const R* Y = c.wt[j][1][dy[r]];
+        const R* Z = c.wt[j][2][dz[r]];
         if (FULL) {
-          const double4 d4 = s.sd[idx], t4 = s.sth[idx];
-          const double2 t2 = s.sth2[idx];
-          double ddx = d4.x, ddy = d4.y, ddz = d4.z;
-          if (vec) {
-            const double4 m = vec[idx];
-            ddx += m.x; ddy += m.y; ddz += m.z;
-          }
-          const R third = R(1.0 / 3.0);
-          amp[0][j] = (R)p.w;
-          amp[1][j] = (R)ddx * sc[0];
-          amp[2][j] = (R)ddy * sc[1];
-          amp[3][j] = (R)ddz * sc[2];
-          amp[4 % NA][j] = (R)t4.x * sc[0] * sc[0] * third;
-          amp[5 % NA][j] = (R)t4.w * sc[1] * sc[1] * third;
-          amp[6 % NA][j] = (R)t2.y * sc[2] * sc[2] * third;
-          amp[7 % NA][j] = R(2) * third * (R)t4.y * sc[0] * sc[1];
-          amp[8 % NA][j] = R(2) * third * (R)t4.z * sc[0] * sc[2];
-          amp[9 % NA][j] = R(2) * third * (R)t2.x * sc[1] * sc[2];
+          const R U0 = fma_(X[2 % NK] * A[4 % NA], Y[0],
+                            fma_(X[0], fma_(A[5 % NA], Y[2 % NK], fma_(A[0], Y[0], A[2] * Y[1])),
+                                 X[1] * fma_(A[1], Y[0], A[7 % NA] * Y[1])));
+          const R U1 = fma_(X[0], fma_(A[3], Y[0], A[9 % NA] * Y[1]), X[1] * A[8 % NA] * Y[0]);
+          const R U2 = X[0] * A[6 % NA] * Y[0];
+          v[r] = fma_(U2, Z[2 % NK], fma_(U0, Z[0], U1 * Z[1]));
         } else {
-          const double4 pv = vec[idx];
-          amp[0][j] = (R)pv.x * sc[0];
-          amp[1][j] = (R)pv.y * sc[1];
-          amp[2][j] = (R)pv.z * sc[2];
+          const R U0 = fma_(A[0] * X[1], Y[0], A[1] * X[0] * Y[1]);
+          const R U1 = A[2] * X[0] * Y[0];
+          v[r] = fma_(U0, Z[0], U1 * Z[1]);
         }
       }
-    }
-    __syncthreads();
-    if (owner) {
-      for (int j = 0; j < n; ++j) {
-        const R x0 = w[0][0][j][cx], x1 = w[0][1][j][cx];
-        const R y0 = w[1][0][j][cy], y1 = w[1][1][j][cy];
-        if (FULL) {
-          const R x2 = w[0][ND][j][cx], y2 = w[1][ND][j][cy];
-          const R U0 = x0 * (amp[0][j] * y0 + amp[2][j] * y1 + amp[5 % NA][j] * y2) +
-                       x1 * (amp[1][j] * y0 + amp[7 % NA][j] * y1) + x2 * amp[4 % NA][j] * y0;
-          const R U1 = x0 * (amp[3][j] * y0 + amp[9 % NA][j] * y1) + x1 * amp[8 % NA][j] * y0;
-          const R U2 = x0 * amp[6 % NA][j] * y0;
-          if (U0 == R(0) && U1 == R(0) && U2 == R(0)) continue;
+      R t[NR];
 #pragma unroll
-          for (int z = 0; z < TM; ++z)
-            acc[z] += U0 * w[2][0][j][z] + U1 * w[2][1][j][z] + U2 * w[2][ND][j][z];
-        } else {
-          const R U0 = amp[0][j] * x1 * y0 + amp[1][j] * x0 * y1;
-          const R U1 = amp[2][j] * x0 * y0;
-          if (U0 == R(0) && U1 == R(0)) continue;
+      for (int r = 0; r < NR; ++r) t[r] = tile[base - off[r]];
 #pragma unroll
-          for (int z = 0; z < TM; ++z) acc[z] += U0 * w[2][0][j][z] + U1 * w[2][1][j][z];
-        }
-      }
+      for (int r = 0; r < NR; ++r) tile[base - off[r]] = t[r] + v[r];
     }
   }
-  if (owner) {
-    R* out = tile_buf<R>(pm) + (size_t)b * pm.tile_size;
-#pragma unroll
-    for (int z = 0; z < TM; ++z)
-      if (z < T2) out[(z * T1 + cy) * T0 + cx] = acc[z];
-  }
+  __syncthreads();
+  R* out = tile_buf<R>(pm) + (size_t)b * pm.tile_size;
+  for (int i = tid; i < size; i += 128) out[i] = tile[i];
 }
 
 template <typename R>
@@ -376,7 +462,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_force(SysView s, PmeView pm, 
 template <int P, bool FULL>
 static void spread_p(const PmeView& pm, const SysView& s, const double4* vec, bool mixed,
                      hipStream_t st) {
-  const dim3 g(pm.nb[0] * pm.nb[1] * pm.nb[2]), bt(kSpreadBlock);
+  const dim3 g(pm.nb[0] * pm.nb[1] * pm.nb[2]), bt(128);
   if (mixed) hipLaunchKernelGGL((k_spread_tile<float, P, FULL>), g, bt, 0, st, s, pm, vec);
   else hipLaunchKernelGGL((k_spread_tile<double, P, FULL>), g, bt, 0, st, s, pm, vec);
 }
