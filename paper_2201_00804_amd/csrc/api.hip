@@ -76,7 +76,8 @@ struct sibfa_ctx_s {
   int* mol_c = nullptr;
   // cells
   int nc[3] = {1, 1, 1}, ncell = 1;
-  int *cell_of = nullptr, *cell_count = nullptr, *cell_start = nullptr, *cursor = nullptr;
+  int2* cell_slot = nullptr;   // cell and slot in it, caller order
+  int *cell_count = nullptr, *cell_start = nullptr, *pol_count = nullptr, *pol_start = nullptr;
   int4* cellmax = nullptr;   // list count maxima per cell and slice
   int *perm = nullptr, *inv_perm = nullptr, *mol_count = nullptr, *mol_s = nullptr;
   int* scan_tmp = nullptr;
@@ -120,7 +121,8 @@ struct sibfa_ctx_s {
   PmeView pm{};
   std::vector<DevBuf> pmebufs;
   int nbricks = 0;
-  int *bcount = nullptr, *bcursor = nullptr, *brick_of = nullptr, *bscan_tmp = nullptr;
+  int *bcount_all = nullptr, *bcount_pol = nullptr, *bscan_tmp = nullptr;
+  int3* bslot = nullptr;   // brick and slots in its two lists, sorted order
   int *bstart_pol = nullptr, *border_pol = nullptr, *bstart_all = nullptr, *border_all = nullptr;
   // cached pol-list pair coefficients (FP64, or FP32 in mixed mode)
   DevBuf coefbuf, icoefbuf, coef32buf;   // FP64 always; FP32 in mixed mode
@@ -583,10 +585,11 @@ sibfa_status alloc_lists(sibfa_ctx c, const int want[4]) {
   return SIBFA_OK;
 }
 
+// cleared: the error word is zero already.
 // beside: enqueued once, right after the first list launch (work for the
 // auxiliary stream that the host should not make the list build wait for).
 template <class Beside>
-sibfa_status build_lists(sibfa_ctx c, Beside beside) {
+sibfa_status build_lists(sibfa_ctx c, bool cleared, Beside beside) {
   int want[4];
   if (c->periodic) {
     const double V = c->box[0] * c->box[1] * c->box[2];
@@ -604,7 +607,7 @@ sibfa_status build_lists(sibfa_ctx c, Beside beside) {
     for (int k = 0; k < 4; ++k) want[k] = std::max(want[k], c->cap[k]);
     sibfa_status st = alloc_lists(c, want);
     if (st != SIBFA_OK) return st;
-    launch_fill_ints({{c->dints + 5, 1}}, 0, c->stream);
+    if (attempt > 0 || !cleared) launch_fill_ints({{c->dints + 5, 1}}, 0, c->stream);
     NlistArgs a{};
     a.periodic = c->periodic;
     for (int d = 0; d < 3; ++d) {
@@ -689,8 +692,9 @@ sibfa_status prepare(sibfa_ctx c) {
   // a re-sort rewrites all per-site records in one pass
   const bool resort = c->dirty_sort;
   if (c->dirty_sort) {
-    launch_fill_ints({{c->cell_count, (size_t)c->ncell + 1}, {c->cursor, (size_t)c->ncell},
-                      {c->mol_count, (size_t)c->n}, {c->dints + 4, 1}}, 0, s);
+    // counters and the error words [4..7]
+    launch_fill_ints({{c->cell_count, (size_t)c->ncell + 1}, {c->pol_count, (size_t)c->ncell + 1},
+                      {c->mol_count, c->ids_ok ? 0 : (size_t)c->n}, {c->dints + 4, 4}}, 0, s);
     BinArgs b{};
     b.n = c->n;
     b.periodic = c->periodic;
@@ -699,19 +703,21 @@ sibfa_status prepare(sibfa_ctx c) {
       b.box[a] = ra.box[a];
       b.ibox[a] = ra.ibox[a];
     }
-    b.xyz = c->xyz_c; b.mol = c->mol_c; b.cell_of = c->cell_of; b.cell_count = c->cell_count;
-    b.mol_count = c->mol_count; b.err = c->dints + 4;
+    b.xyz = c->xyz_c; b.mol = c->mol_c; b.alpha = c->alpha_c;
+    b.cell_slot = c->cell_slot; b.cell_count = c->cell_count; b.pol_count = c->pol_count;
+    b.mol_count = c->ids_ok ? nullptr : c->mol_count; b.err = c->dints + 4;
     {
       Phase ph(c, SIBFA_PH_LISTS);
       launch_bin(b, s);
       if (c->periodic) {
-        launch_exclusive_scan(c->cell_count, c->cell_start, c->ncell + 1, c->scan_tmp, s);
-        launch_scatter(c->cell_of, c->cell_start, c->cursor, c->perm, c->n, s);
-        launch_sort_cells(c->cell_start, c->ncell, c->perm, s);
+        launch_exclusive_scan2(c->cell_count, c->cell_start, c->pol_count, c->pol_start,
+                               c->ncell + 1, c->scan_tmp, s);
+        launch_scatter(c->cell_slot, c->cell_start, c->perm, c->n, s);
+        launch_cell_records(ra, c->cell_start, c->pol_start, c->ncell, c->perm, s);
       } else {
         launch_one_cell(c->perm, c->cell_start, c->n, s);
+        launch_rec_all(ra, s);
       }
-      launch_rec_all(ra, s);
     }
     if (!c->ids_ok) {
       HIP_TRY(hipMemcpyAsync(c->h_ints + 4, c->dints + 4, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -730,16 +736,23 @@ sibfa_status prepare(sibfa_ctx c) {
     c->e0_valid = false;
   }
   if (c->dirty_pol) {
-    launch_fill_int(c->dints + 7, 0, 1, s);
-    if (!resort) launch_rec_pol(ra, s);
-    launch_exclusive_scan(c->is_pol, c->pol_scan, c->n + 1, c->scan_tmp, s);
-    launch_rec_polsites(ra, s);
+    // a periodic re-sort has written the polarizable records with the rest
+    const int* total = c->pol_start + c->ncell;
+    if (!(resort && c->periodic)) {
+      if (!resort) {
+        launch_fill_int(c->dints + 7, 0, 1, s);
+        launch_rec_pol(ra, s);
+      }
+      launch_exclusive_scan(c->is_pol, c->pol_scan, c->n + 1, c->scan_tmp, s);
+      launch_rec_polsites(ra, s);
+      total = c->pol_scan + c->n;
+    }
     // a re-sort permutes the same polarizabilities: count, definiteness
     // and extents are unchanged
     if (!c->pol_ok) {
       double* dext = reinterpret_cast<double*>(c->dints + 32);
       launch_pol_extents(ra, dext, s);
-      HIP_TRY(hipMemcpyAsync(c->h_ints, c->pol_scan + c->n, sizeof(int), hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipMemcpyAsync(c->h_ints, total, sizeof(int), hipMemcpyDeviceToHost, s));
       HIP_TRY(hipMemcpyAsync(c->h_ints + 7, c->dints + 7, sizeof(int), hipMemcpyDeviceToHost, s));
       HIP_TRY(hipMemcpyAsync(c->h_pinned + 56, dext, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
       sibfa_status st = sync_read(c);
@@ -781,21 +794,17 @@ sibfa_status prepare(sibfa_ctx c) {
       if (two) (void)hipStreamWaitEvent(a, c->ev_fork, 0);
       {
         Phase ph(c, SIBFA_PH_LISTS, a);
-        SysView sv = make_view(c);
-        for (int pol = 0; pol < 2; ++pol) {
-          int* start = pol ? c->bstart_pol : c->bstart_all;
-          int* order = pol ? c->border_pol : c->border_all;
-          const int cnt = pol ? c->npol : c->n;
-          launch_fill_ints({{c->bcount, (size_t)c->nbricks + 1}, {c->bcursor, (size_t)c->nbricks}},
-                           0, a);
-          launch_brick_bin(sv, c->pm, pol, c->brick_of, c->bcount, a);
-          launch_exclusive_scan(c->bcount, start, c->nbricks + 1, c->bscan_tmp, a);
-          if (cnt > 0) {
-            launch_scatter(c->brick_of, start, c->bcursor, order, cnt, a);
-            // increasing site index within each brick: reproducible sums
-            launch_sort_cells(start, c->nbricks, order, a);
-          }
-        }
+        const SysView sv = make_view(c);
+        const size_t nb = (size_t)c->nbricks + 1;
+        launch_fill_ints({{c->bcount_all, nb}, {c->bcount_pol, nb}}, 0, a);
+        launch_brick_bin(sv, c->pm, c->bslot, c->bcount_all, c->bcount_pol, a);
+        launch_exclusive_scan2(c->bcount_all, c->bstart_all, c->bcount_pol, c->bstart_pol, (int)nb,
+                               c->bscan_tmp, a);
+        launch_brick_scatter(sv, c->bslot, c->bstart_all, c->border_all, c->bstart_pol,
+                             c->border_pol, a);
+        // increasing site index within each brick: reproducible sums
+        launch_sort_segments(c->bstart_all, c->border_all, c->bstart_pol, c->border_pol,
+                             c->nbricks, a);
       }
       if (two) {
         (void)hipEventRecord(c->ev_bricks, a);
@@ -806,7 +815,7 @@ sibfa_status prepare(sibfa_ctx c) {
       conv(c, false, a, S_EREC0);
       c->phi_e0 = true;
     };
-    sibfa_status st = build_lists(c, beside_lists);
+    sibfa_status st = build_lists(c, resort, beside_lists);
     if (st != SIBFA_OK) return st;
     c->dirty_lists = false;
     c->e0_valid = false;
@@ -1524,9 +1533,9 @@ sibfa_status setup_pme(sibfa_ctx c) {
   pm.tile_size = (pm.Bb[0] + order - 1) * (pm.Bb[1] + order - 1) * (pm.Bb[2] + order - 1);
   {
     const size_t nbk = (size_t)c->nbricks;
-    if (!alloc_into(c, c->pmebufs, c->bcount, nbk + 1) ||
-        !alloc_into(c, c->pmebufs, c->bcursor, nbk) ||
-        !alloc_into(c, c->pmebufs, c->brick_of, (size_t)c->n) ||
+    if (!alloc_into(c, c->pmebufs, c->bcount_all, nbk + 1) ||
+        !alloc_into(c, c->pmebufs, c->bcount_pol, nbk + 1) ||
+        !alloc_into(c, c->pmebufs, c->bslot, (size_t)c->n) ||
         !alloc_into(c, c->pmebufs, c->bscan_tmp, scan_temp_ints((int)nbk + 1) + 16) ||
         !alloc_into(c, c->pmebufs, c->bstart_pol, nbk + 1) ||
         !alloc_into(c, c->pmebufs, c->border_pol, (size_t)c->n) ||
@@ -1701,7 +1710,7 @@ size_t sibfa_footprint_bytes(int n_sites, int n_polarizable, const double* box,
   size_t bytes = 0;
   bytes += n * (3 + 1 + 3 + 6 + 6 + 1 + 3) * sizeof(double);        // caller copies
   bytes += n * (4 + 4 + 4 + 2) * sizeof(double) + n * (4 + 4 + 4 + 2) * sizeof(float);
-  bytes += n * 12 * sizeof(int) + n * (1 + 6 + 6) * sizeof(double) + n * 24;  // pol arrays
+  bytes += n * 15 * sizeof(int) + n * (1 + 6 + 6) * sizeof(double) + n * 24;  // pol arrays
   bytes += n * (2 * 32 + 16);                                         // mu_s, Freal
   bytes += np * (7 * 32 + 2 * 16);                                    // solver vectors
   size_t cap_all, cap_pol;
@@ -1721,11 +1730,11 @@ size_t sibfa_footprint_bytes(int n_sites, int n_polarizable, const double* box,
       tiles *= (size_t)((p->grid[a] + e - 1) / e) * (e + p->order - 1);
     }
     bytes += tiles * (8 + 4);
-    // cell grid as in sibfa_set_system: count, start, cursor; list maxima
+    // cell grid as in sibfa_set_system: two counts, two starts; list maxima
     size_t cells = 1;
     for (int a = 0; a < 3; ++a)
       cells *= (size_t)std::max(1, std::min(1024, (int)std::floor(box[a] / (0.5 * p->cutoff))));
-    bytes += cells * 3 * sizeof(int) +
+    bytes += cells * 4 * sizeof(int) +
              cells * (size_t)nlist_slices((int)n, (int)cells) * sizeof(int4);
   } else {
     cap_all = n;
@@ -1773,8 +1782,10 @@ sibfa_status sibfa_set_system(sibfa_ctx c, int n_sites, const double* xyz, const
             alloc_into(c, L, c->dip_c, 3 * n) && alloc_into(c, L, c->quad_c, 6 * n) &&
             alloc_into(c, L, c->alpha_c, 6 * n) && alloc_into(c, L, c->thole_c, n) &&
             alloc_into(c, L, c->mu_c, 3 * n) && alloc_into(c, L, c->mol_c, n) &&
-            alloc_into(c, L, c->cell_of, n) && alloc_into(c, L, c->cell_count, c->ncell + 1) &&
-            alloc_into(c, L, c->cell_start, c->ncell + 1) && alloc_into(c, L, c->cursor, c->ncell) &&
+            alloc_into(c, L, c->cell_slot, n) && alloc_into(c, L, c->cell_count, c->ncell + 1) &&
+            alloc_into(c, L, c->cell_start, c->ncell + 1) &&
+            alloc_into(c, L, c->pol_count, c->ncell + 1) &&
+            alloc_into(c, L, c->pol_start, c->ncell + 1) &&
             alloc_into(c, L, c->cellmax, (size_t)c->ncell * nlist_slices(n_sites, c->ncell)) &&
             alloc_into(c, L, c->perm, n) && alloc_into(c, L, c->inv_perm, n) &&
             alloc_into(c, L, c->mol_count, n) && alloc_into(c, L, c->mol_s, n) &&

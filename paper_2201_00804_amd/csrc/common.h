@@ -221,25 +221,28 @@ __device__ __forceinline__ int xcd_block() {
 }
 // For every active lane, adds 1 to base[key], with one atomic per distinct
 // key of the wavefront (sorted or clustered keys make that a few atomics
-// instead of one per lane on the same address); returns the lane's slot,
-// the counter's old value plus the number of lower active lanes with the
-// same key.  Every lane of the wavefront must call it.
+// instead of one per lane on the same address), all of them issued together;
+// returns the lane's slot, the counter's old value plus the number of lower
+// active lanes with the same key.  Every lane of the wavefront must call it.
 __device__ __forceinline__ int wave_atomic_inc(int* base, int key, bool active) {
   const int lane = threadIdx.x & 63;
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   unsigned long long todo = __ballot(active);
-  int slot = 0;
+  int first = 0, rank = 0, count = 0;   // of this lane's key in the wavefront
   while (todo) {
     const int leader = __builtin_ctzll(todo);
-    const int k = __shfl(key, leader, 64);
+    const int k = __builtin_amdgcn_readlane(key, leader);
     const unsigned long long same = __ballot(active && key == k);
-    int old = 0;
-    if (lane == leader) old = atomicAdd(&base[k], __popcll(same));
-    old = __shfl(old, leader, 64);
-    if (active && key == k) slot = old + __popcll(same & below);
+    if (active && key == k) {
+      first = leader;
+      rank = __popcll(same & below);
+      count = __popcll(same);
+    }
     todo &= ~same;
   }
-  return slot;
+  int old = 0;
+  if (active && lane == first) old = atomicAdd(&base[key], count);
+  return __shfl(old, first, 64) + rank;
 }
 // base + the number of set bits of mask below this lane
 __device__ __forceinline__ int lanes_below(unsigned long long mask, int base) {
@@ -418,5 +421,9 @@ void launch_fill_double(double* p, double v, size_t n, hipStream_t s);
 void launch_fill_float(float* p, float v, size_t n, hipStream_t s);
 size_t scan_temp_ints(int n);
 void launch_exclusive_scan(const int* in, int* out, int n, int* tmp, hipStream_t s);
+// two scans of the same length, in one launch where one workgroup scans each
+// (the longer ones one after the other, sharing tmp)
+void launch_exclusive_scan2(const int* in0, int* out0, const int* in1, int* out1, int n, int* tmp,
+                            hipStream_t s);
 
 }  // namespace sibfa

@@ -36,10 +36,13 @@ void launch_force(const SysView& s, Reduce& red, const double4* mu, const float4
 // when mu != NULL, sorted-site indexing) onto the real grid.
 void launch_spread_mult(const SysView& s, const PmeView& pm, const double4* mu, bool mixed,
                         hipStream_t st);
-// Home-brick binning of the sites for the spreading kernels (counts must be
-// zeroed; pol = 1 bins polarizable sites, 0 all sites).
-void launch_brick_bin(const SysView& s, const PmeView& pm, int pol, int* brick_of, int* counts,
-                      hipStream_t st);
+// Home-brick binning of all sites and of the polarizable ones for the
+// spreading kernels (counts must be zeroed), then, from the counts' scans,
+// each brick's sites in the order the counters gave out.
+void launch_brick_bin(const SysView& s, const PmeView& pm, int3* slot, int* count_all,
+                      int* count_pol, hipStream_t st);
+void launch_brick_scatter(const SysView& s, const int3* slot, const int* start_all, int* order_all,
+                          const int* start_pol, int* order_pol, hipStream_t st);
 // Real grid Q from the spreading tiles (used by the multi-pass convolution).
 void launch_spread_fold(const PmeView& pm, bool mixed, hipStream_t st);
 // Spread of the polarizable-site dipoles p (polarizable order).

@@ -11,9 +11,13 @@ struct BinArgs {
   double box[3], ibox[3];
   const double* xyz;     // caller order [n][3]
   const int* mol;        // caller order [n]
-  int* cell_of;          // [n]
-  int* cell_count;       // [ncell + 1], zeroed
-  int* mol_count;        // [n], zeroed
+  const double* alpha;   // caller order [n][6]
+  // periodic only: cell and slot in it, counts of all and of polarizable
+  // sites per cell (zeroed)
+  int2* cell_slot;       // [n]
+  int* cell_count;       // [ncell + 1]
+  int* pol_count;        // [ncell + 1]
+  int* mol_count;        // [n], zeroed, or nullptr: already counted
   int* err;              // bit 2: molecule id out of range; bit 8: NaN/Inf position
 };
 
@@ -72,9 +76,15 @@ void launch_bin(const BinArgs& a, hipStream_t s);
 void launch_cellmax_reduce(const int4* cellmax, int count, int* out, hipStream_t s);
 // One cell holding every site in caller order: perm[i] = i, cell_start = {0, n}.
 void launch_one_cell(int* perm, int* cell_start, int n, hipStream_t s);
-void launch_scatter(const int* cell_of, const int* cell_start, int* cursor, int* perm,
-                    int n, hipStream_t s);
-void launch_sort_cells(const int* cell_start, int ncell, int* perm, hipStream_t s);
+void launch_scatter(const int2* cell_slot, const int* cell_start, int* perm, int n,
+                    hipStream_t s);
+// increasing order within each of the nseg segments of two lists
+void launch_sort_segments(const int* start0, int* v0, const int* start1, int* v1, int nseg,
+                          hipStream_t s);
+// periodic re-sort: cells sorted by caller index, all records, polarizable
+// indices (from pol_start, the scan of the cells' polarizable counts)
+void launch_cell_records(const RecArgs& a, const int* cell_start, const int* pol_start, int ncell,
+                         int* perm, hipStream_t s);
 void launch_sum_ints(const int* v, int n, unsigned long long* out, hipStream_t s);
 // positions, multipoles and polarizability records in one pass (after a
 // re-sort, when all three change)

@@ -124,7 +124,15 @@ __global__ void k_scan_add(int* out, int n, const int* tile_offsets) {
 // One launch instead of the three of the multi-block form.
 constexpr int kScanBig = 1024;
 constexpr int kScanSingleMax = 4 * 4 * kScanBig;   // larger scans: the multi-block form is faster
-__global__ __launch_bounds__(kScanBig) void k_scan_single(const int* in, int* out, int n) {
+struct ScanArgs {
+  const int* in[2];
+  int* out[2];
+  int n;
+};
+__global__ __launch_bounds__(kScanBig) void k_scan_single(ScanArgs a) {
+  const int* in = a.in[blockIdx.x];
+  int* out = a.out[blockIdx.x];
+  const int n = a.n;
   __shared__ int wsum[kScanBig / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   int carry = 0;
@@ -170,7 +178,8 @@ void launch_exclusive_scan(const int* in, int* out, int n, int* tmp, hipStream_t
   if (n <= 0) return;
   const int tiles = (n + kScanTile - 1) / kScanTile;
   if (tiles > 1 && n <= kScanSingleMax) {
-    hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(kScanBig), 0, s, in, out, n);
+    const ScanArgs a = {{in, nullptr}, {out, nullptr}, n};
+    hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(kScanBig), 0, s, a);
     return;
   }
   hipLaunchKernelGGL(k_scan_tiles, dim3(tiles), dim3(kBlock), 0, s, in, out, n, tmp);
@@ -178,6 +187,18 @@ void launch_exclusive_scan(const int* in, int* out, int n, int* tmp, hipStream_t
   launch_exclusive_scan(tmp, tmp + tiles, tiles, tmp + 2 * tiles, s);
   hipLaunchKernelGGL(k_scan_add, dim3(tiles), dim3(kBlock), 0, s, out, n,
                      (const int*)(tmp + tiles));
+}
+
+void launch_exclusive_scan2(const int* in0, int* out0, const int* in1, int* out1, int n, int* tmp,
+                            hipStream_t s) {
+  if (n <= 0) return;
+  if (n <= kScanSingleMax) {
+    const ScanArgs a = {{in0, in1}, {out0, out1}, n};
+    hipLaunchKernelGGL(k_scan_single, dim3(2), dim3(kScanBig), 0, s, a);
+    return;
+  }
+  launch_exclusive_scan(in0, out0, n, tmp, s);
+  launch_exclusive_scan(in1, out1, n, tmp, s);
 }
 
 // ------------------------------------------------------------ binning
@@ -191,9 +212,20 @@ __device__ __forceinline__ double wrap(double x, double L, double iL) {
   return (w > -L && w < L) ? w : 0.0;
 }
 
+// Polarizable: a nonzero tensor.
+__device__ __forceinline__ bool nonzero6(const double* al) {
+  bool pol = false;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) pol = pol || al[k] != 0.0;
+  return pol;
+}
+
 // Neighbouring caller indices are usually neighbouring sites (a molecule's
 // sites, molecules laid out in space order), so the counters are
-// incremented per wavefront run of equal keys.
+// incremented per wavefront run of equal keys.  A site's slot in its cell is
+// the old value of the cell's counter (in no particular order: the cells are
+// sorted afterwards); a second counter takes the cell's polarizable sites.
+// Molecules are counted once per set of ids (mol_count given).
 __global__ void k_bin(BinArgs a) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   const bool act = c < a.n;
@@ -213,57 +245,63 @@ __global__ void k_bin(BinArgs a) {
       }
       cell = ci[0] + a.nc[0] * (ci[1] + a.nc[1] * ci[2]);
     }
-    a.cell_of[c] = cell;
     m = a.mol[c];
     if (!(m >= 0 && m < a.n)) atomicOr(a.err, 2);
   }
-  wave_atomic_inc(a.cell_count, cell, act);
-  wave_atomic_inc(a.mol_count, m, act && m >= 0 && m < a.n);
+  if (a.periodic) {
+    const int slot = wave_atomic_inc(a.cell_count, cell, act);
+    if (act) a.cell_slot[c] = make_int2(cell, slot);
+    wave_atomic_inc(a.pol_count, cell, act && nonzero6(a.alpha + 6 * (size_t)c));
+  }
+  if (a.mol_count) wave_atomic_inc(a.mol_count, m, act && m >= 0 && m < a.n);
 }
 
-// Slots within a key come from wavefront runs and one atomic per run; their
-// order across wavefronts is fixed afterwards by k_sort_cells.
-__global__ void k_scatter(const int* cell_of, const int* cell_start, int* cursor,
-                          int* perm, int n) {
+__global__ void k_scatter(const int2* cell_slot, const int* cell_start, int* perm, int n) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  const bool act = c < n;
-  const int cell = act ? cell_of[c] : 0;
-  const int slot = wave_atomic_inc(cursor, cell, act);
-  if (act) perm[cell_start[cell] + slot] = c;
+  if (c >= n) return;
+  const int2 q = cell_slot[c];
+  perm[cell_start[q.x] + q.y] = c;
 }
 
-// One thread per cell: insertion sort of the cell's segment by caller index.
-// Sorts each cell's entries of perm (distinct site indices) in increasing
-// order, which makes the cell-sorted order independent of the order in
-// which the scatter's atomics ran.  One wavefront per cell: the entries are
-// ranked in LDS (rank = number of smaller entries); cells too large for the
-// LDS buffer fall back to an insertion sort by one lane.
+// Sorts the n entries at seg (distinct indices) in increasing order by one
+// wavefront, which makes the order independent of the order in which the
+// binning's atomics ran: the entries are ranked in LDS (rank = number of
+// smaller entries); segments too large for the LDS buffer fall back to an
+// insertion sort by one lane.
 constexpr int kSortLds = 256;
-__global__ __launch_bounds__(64) void k_sort_cells(const int* cell_start, int ncell, int* perm) {
-  __shared__ int v[kSortLds];
-  const int cell = blockIdx.x;
-  if (cell >= ncell) return;
-  const int s = cell_start[cell], e = cell_start[cell + 1], n = e - s;
+__device__ __forceinline__ void sort_segment(int* seg, int n, int* v) {
   if (n <= kSortLds) {
-    for (int k = threadIdx.x; k < n; k += 64) v[k] = perm[s + k];
+    for (int k = threadIdx.x; k < n; k += 64) v[k] = seg[k];
     __syncthreads();
     for (int k = threadIdx.x; k < n; k += 64) {
       const int x = v[k];
       int r = 0;
       for (int m = 0; m < n; ++m) r += v[m] < x ? 1 : 0;
-      perm[s + r] = x;
+      seg[r] = x;
     }
   } else if (threadIdx.x == 0) {
-    for (int i = s + 1; i < e; ++i) {
-      const int x = perm[i];
+    for (int i = 1; i < n; ++i) {
+      const int x = seg[i];
       int j = i - 1;
-      while (j >= s && perm[j] > x) {
-        perm[j + 1] = perm[j];
+      while (j >= 0 && seg[j] > x) {
+        seg[j + 1] = seg[j];
         --j;
       }
-      perm[j + 1] = x;
+      seg[j + 1] = x;
     }
   }
+}
+
+// Segments of two lists, one wavefront each: blocks [0, nseg) those of the
+// first, [nseg, 2 nseg) those of the second.
+__global__ __launch_bounds__(64) void k_sort_segments(const int* start0, int* v0,
+                                                      const int* start1, int* v1, int nseg) {
+  __shared__ int v[kSortLds];
+  const bool second = (int)blockIdx.x >= nseg;
+  const int b = blockIdx.x - (second ? nseg : 0);
+  const int* start = second ? start1 : start0;
+  int* perm = second ? v1 : v0;
+  sort_segment(perm + start[b], start[b + 1] - start[b], v);
 }
 
 // Clusters: one cell in caller order, what the counting sort would give
@@ -298,13 +336,14 @@ void launch_sum_ints(const int* v, int n, unsigned long long* out, hipStream_t s
 void launch_bin(const BinArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_bin, dim3((a.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a);
 }
-void launch_scatter(const int* cell_of, const int* cell_start, int* cursor, int* perm,
-                    int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_scatter, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                     cell_of, cell_start, cursor, perm, n);
+void launch_scatter(const int2* cell_slot, const int* cell_start, int* perm, int n,
+                    hipStream_t s) {
+  hipLaunchKernelGGL(k_scatter, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, cell_slot,
+                     cell_start, perm, n);
 }
-void launch_sort_cells(const int* cell_start, int ncell, int* perm, hipStream_t s) {
-  hipLaunchKernelGGL(k_sort_cells, dim3(ncell), dim3(64), 0, s, cell_start, ncell, perm);
+void launch_sort_segments(const int* start0, int* v0, const int* start1, int* v1, int nseg,
+                          hipStream_t s) {
+  hipLaunchKernelGGL(k_sort_segments, dim3(2 * nseg), dim3(64), 0, s, start0, v0, start1, v1, nseg);
 }
 // ------------------------------------------------------------ records
 // Positions (wrapped when periodic) and molecule ids in sorted order; the
@@ -340,9 +379,8 @@ __device__ __forceinline__ void rec_mult_store(const RecArgs& a, int i, const do
 // Polarizability of caller site c: s = abar^-1/2 (0 when not polarizable);
 // writes the Thole factor and the polarizable flag of sorted site i.
 __device__ __forceinline__ double rec_pol_of(const RecArgs& a, int i, int c) {
-  const double* al = a.alpha + 6 * c;
-  bool pol = false;
-  for (int k = 0; k < 6; ++k) pol = pol || (al[k] != 0.0);
+  const double* al = a.alpha + 6 * (size_t)c;
+  const bool pol = nonzero6(al);
   const double abar = (al[0] + al[3] + al[5]) / 3.0;
   a.sa[i] = a.thole ? a.thole[c] : a.thole_default;
   a.is_pol[i] = pol ? 1 : 0;
@@ -383,11 +421,8 @@ __global__ void k_rec_pol(RecArgs a) {
   a.sd32[i] = dd32;
 }
 
-// After a re-sort all three records change: one pass writes them whole.
-__global__ void k_rec_all(RecArgs a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n) return;
-  const int c = a.perm[i];
+// After a re-sort all three records change: written whole.
+__device__ __forceinline__ void rec_all_of(const RecArgs& a, int i, int c) {
   double x[3], q, d[3], t[6];
   rec_pos_of(a, i, c, x);
   rec_mult_of(a, c, q, d, t);
@@ -399,17 +434,15 @@ __global__ void k_rec_all(RecArgs a) {
   rec_mult_store(a, i, d, t);
 }
 
-// After the scan of is_pol: polarizable index maps and polarizable records,
-// including alpha^-1 (checked symmetric positive definite).
-__global__ void k_rec_polsites(RecArgs a) {
+__global__ void k_rec_all(RecArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n) return;
-  const bool pol = a.is_pol[i] != 0;
-  const int pi = a.pol_scan[i];
-  a.polidx[i] = pol ? pi : -1;
-  if (!pol) return;
+  if (i < a.n) rec_all_of(a, i, a.perm[i]);
+}
+
+// Polarizable records of sorted site i (caller site c) at polarizable index
+// pi, including alpha^-1 (checked symmetric positive definite).
+__device__ __forceinline__ void rec_polsite_of(const RecArgs& a, int i, int c, int pi) {
   a.polsite[pi] = i;
-  const int c = a.perm[i];
   const double4 p = a.sp[i];
   const double s = a.sd[i].w;
   a.pp[pi] = make_double4(p.x, p.y, p.z, s);
@@ -417,6 +450,7 @@ __global__ void k_rec_polsites(RecArgs a) {
   a.pa[pi] = a.sa[i];
   const double* al = a.alpha + 6 * c;
   const double xx = al[0], xy = al[1], xz = al[2], yy = al[3], yz = al[4], zz = al[5];
+#pragma unroll
   for (int k = 0; k < 6; ++k) a.alpha_s[6 * pi + k] = al[k];
   // Cholesky-type positivity test: leading principal minors > 0
   const double m1 = xx, m2 = xx * yy - xy * xy;
@@ -431,6 +465,50 @@ __global__ void k_rec_polsites(RecArgs a) {
   a.ainv_s[6 * pi + 5] = (xx * yy - xy * xy) * id;
 }
 
+// After the scan of is_pol: polarizable index maps and records.
+__global__ void k_rec_polsites(RecArgs a) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  const bool pol = a.is_pol[i] != 0;
+  const int pi = a.pol_scan[i];
+  a.polidx[i] = pol ? pi : -1;
+  if (pol) rec_polsite_of(a, i, a.perm[i], pi);
+}
+
+// A cell's sites (periodic re-sort), one wavefront per cell: sorted by caller
+// index, then every record and polarizable index in one pass.  Sort, records,
+// a scan over all sites and the polarizable records were four to six
+// launches, each little more than its launch time below 32,000 waters; with
+// the two brick lists binned together (15 launches fewer in all) a step of
+// 216 waters went from 1211 to 1166 us, of 32,000 from 4933 to 4903 us.
+__global__ __launch_bounds__(64) void k_cell_records(RecArgs a, const int* cell_start,
+                                                     const int* pol_start, int* perm) {
+  __shared__ int v[kSortLds];
+  const int cell = blockIdx.x, lane = threadIdx.x;
+  const int s = cell_start[cell], n = cell_start[cell + 1] - s;
+  sort_segment(perm + s, n, v);
+  __syncthreads();
+  int run = pol_start[cell];
+  for (int k0 = 0; k0 < n; k0 += 64) {
+    const int i = s + k0 + lane;
+    const bool on = k0 + lane < n;
+    const int c = on ? perm[i] : 0;
+    const bool pol = on && nonzero6(a.alpha + 6 * (size_t)c);
+    const unsigned long long m = __ballot(pol);
+    if (on) {
+      rec_all_of(a, i, c);
+      const int pi = lanes_below(m, run);
+      a.polidx[i] = pol ? pi : -1;
+      if (pol) rec_polsite_of(a, i, c, pi);
+    }
+    run += __popcll(m);
+  }
+}
+
+void launch_cell_records(const RecArgs& a, const int* cell_start, const int* pol_start, int ncell,
+                         int* perm, hipStream_t s) {
+  hipLaunchKernelGGL(k_cell_records, dim3(ncell), dim3(64), 0, s, a, cell_start, pol_start, perm);
+}
 void launch_rec_all(const RecArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_rec_all, dim3((a.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a);
 }

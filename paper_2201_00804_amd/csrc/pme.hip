@@ -39,16 +39,17 @@ __device__ __forceinline__ float grid_phi<float>(const PmeView& pm, size_t idx) 
 //                  starts from.
 
 // Sites come in cell-sorted order, so a wavefront's sites fall in a few
-// bricks: one counter atomic per run of equal bricks.
-__global__ void k_brick_bin(SysView s, PmeView pm, int pol, int* brick_of, int* counts) {
+// bricks: one counter atomic per run of equal bricks.  One pass bins all
+// sites and, among them, the polarizable ones (slot: brick, slot in the
+// brick's list of all sites and in that of its polarizable sites).
+__global__ void k_brick_bin(SysView s, PmeView pm, int3* slot, int* count_all, int* count_pol) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = pol ? s.npol : s.n;
-  const bool act = i < n;
-  int b = 0;
+  const bool act = i < s.n;
+  int b = 0, pi = -1;
   if (act) {
-    double x[3];
-    if (pol) { const double4 p = s.pp[i]; x[0] = p.x; x[1] = p.y; x[2] = p.z; }
-    else { const double4 p = s.sp[i]; x[0] = p.x; x[1] = p.y; x[2] = p.z; }
+    const double4 p = s.sp[i];
+    pi = s.polidx[i];
+    const double x[3] = {p.x, p.y, p.z};
     int h[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -56,17 +57,32 @@ __global__ void k_brick_bin(SysView s, PmeView pm, int pol, int* brick_of, int* 
       h[a] = grid_base(x[a], pm.scale[a], pm.K[a], &fr) / pm.Bb[a];
     }
     b = h[0] + pm.nb[0] * (h[1] + pm.nb[1] * h[2]);
-    brick_of[i] = b;
   }
-  wave_atomic_inc(counts, b, act);
+  const int sa = wave_atomic_inc(count_all, b, act);
+  const int sp = wave_atomic_inc(count_pol, b, act && pi >= 0);
+  if (act) slot[i] = make_int3(b, sa, sp);
 }
 
-void launch_brick_bin(const SysView& s, const PmeView& pm, int pol, int* brick_of, int* counts,
-                      hipStream_t st) {
-  const int n = pol ? s.npol : s.n;
-  if (n > 0)
-    hipLaunchKernelGGL(k_brick_bin, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, s, pm,
-                       pol, brick_of, counts);
+__global__ void k_brick_scatter(SysView s, const int3* slot, const int* start_all, int* order_all,
+                                const int* start_pol, int* order_pol) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= s.n) return;
+  const int3 q = slot[i];
+  order_all[start_all[q.x] + q.y] = i;
+  const int pi = s.polidx[i];
+  if (pi >= 0) order_pol[start_pol[q.x] + q.z] = pi;
+}
+
+void launch_brick_bin(const SysView& s, const PmeView& pm, int3* slot, int* count_all,
+                      int* count_pol, hipStream_t st) {
+  hipLaunchKernelGGL(k_brick_bin, dim3((s.n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, s, pm,
+                     slot, count_all, count_pol);
+}
+
+void launch_brick_scatter(const SysView& s, const int3* slot, const int* start_all, int* order_all,
+                          const int* start_pol, int* order_pol, hipStream_t st) {
+  hipLaunchKernelGGL(k_brick_scatter, dim3((s.n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, s,
+                     slot, start_all, order_all, start_pol, order_pol);
 }
 
 template <typename R>
