@@ -7,7 +7,9 @@ The variable is t = 1 / (1 + P x) mapped to u in [-1, 1]; the series is a
 least-squares fit in relative error at Chebyshev nodes of u, against
 scipy.special.erfcx.  Beyond XMAX the kernels clamp x (erfc(6) = 2e-17, so
 the clamped value is off by a relative factor below x / XMAX on numbers
-under 2e-17).
+under 2e-17).  The FP64 series is also written as powers of u, and with it
+the polynomial q of exp(r) = 1 + r + r^2 q(r), |r| <= ln(2) / 2, fitted the
+same way to the sum of r^k / (k + 2)!.
 
     python paper_2201_00804_amd/csrc/gen_erfcx.py   # rewrites erfcx_fit.h
 """
@@ -15,10 +17,11 @@ import os
 
 import numpy as np
 from numpy.polynomial import chebyshev as C
-from scipy.special import erfcx
+from scipy.special import erfcx, factorial
 
 XMAX = 6.0
 FITS = {"double": (16, 0.2), "float": (8, 0.8)}   # degree, P
+EXP_DEG = 9
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -33,6 +36,22 @@ def fit(deg, p, npts=6000):
     ts = 1.0 / (1.0 + p * xs)
     rel = np.abs(C.chebval(2.0 * (ts - t0) / (1.0 - t0) - 1.0, c) / erfcx(xs) - 1.0)
     return t0, c, float(rel.max())
+
+
+def fit_exp(deg, npts=6000):
+    h = 0.5 * np.log(2.0)
+    k = np.arange(npts)
+    u = np.cos(np.pi * (k + 0.5) / npts)
+    y = sum((h * u) ** m / factorial(m + 2) for m in range(20))
+    c = C.cheb2poly(C.chebfit(u, y, deg)) / h ** np.arange(deg + 1)
+    r = (h * np.linspace(-1.0, 1.0, 200001)).astype(np.longdouble)
+    q = sum(np.longdouble(v) * r ** m for m, v in enumerate(c))
+    return c, float(np.abs((1 + r + r * r * q) / np.exp(r) - 1).max())
+
+
+def array(name, c):
+    return [f"constexpr double {name}[{len(c)}] = {{"] + [f"    {float(v)!r}," for v in c] + \
+        ["};", ""]
 
 
 def main():
@@ -52,6 +71,12 @@ def main():
         lines += [f"    {float(v)!r}{sfx}," for v in c]
         lines += ["};", ""]
         print(f"{ty}: degree {deg}, p {p}, max relative error {err:.2e}")
+        if name == "F64":
+            lines += ["// the same series as powers of u"] + array("kErfcxMF64", C.cheb2poly(c))
+    c, err = fit_exp(EXP_DEG)
+    lines += ["// exp(r) = 1 + r + r^2 q(r), |r| <= ln(2) / 2: powers of r of q;",
+              f"// largest relative error {err:.1e}",
+              f"constexpr int kExpDeg = {EXP_DEG};"] + array("kExpQ", c)
     lines += ["}  // namespace sibfa", ""]
     with open(os.path.join(HERE, "erfcx_fit.h"), "w") as f:
         f.write("\n".join(lines))

@@ -211,6 +211,64 @@ __device__ __forceinline__ void perm_pair(const SysView& s, int i, int j, int pi
   }
 }
 
+// FP64 pairs: a site's record as loaded, one entry ahead of its use (few
+// wavefronts fit beside the sums: without it the force takes 855 us, not 810).
+struct SiteRec {
+  double4 p, d, t;
+  double2 t2;
+};
+__device__ __forceinline__ SiteRec site_rec(const SysView& s, int j) {
+  return {s.sp[j], s.sd[j], s.sth[j], s.sth2[j]};
+}
+__device__ __forceinline__ void rec_mp(const SiteRec& r, MP<double>& M, double x[3]) {
+  x[0] = r.p.x; x[1] = r.p.y; x[2] = r.p.z;
+  M.q = r.p.w;
+  M.d[0] = r.d.x; M.d[1] = r.d.y; M.d[2] = r.d.z;
+  M.t[0] = r.t.x; M.t[1] = r.t.y; M.t[2] = r.t.z; M.t[3] = r.t.w; M.t[4] = r.t2.x; M.t[5] = r.t2.y;
+}
+// Entry k of a site's list, near ones (nn) first.
+__device__ __forceinline__ int list_entry(const int* row, int cap, int nn, int k) {
+  return row[k < nn ? k : nn + cap - 1 - k];
+}
+
+// One pair of k_perm in FP64: the undamped potential of M_j and its
+// derivatives are summed (energy and field follow per site), the damping's
+// part of the field is taken off acc.
+__device__ __forceinline__ void perm_pair_pot(const SysView& s, int i, int j, const SiteRec& rec,
+                                              bool near, const double xi[3], double si,
+                                              double& phi, PotSums& P, double acc[3]) {
+  MP<double> Mj;
+  double Rv[3], xj[3], c[6];
+  rec_mp(rec, Mj, xj);
+  displacement<double>(s, xi, xj, Rv);
+  const double r2 = Rv[0] * Rv[0] + Rv[1] * Rv[1] + Rv[2] * Rv[2];
+  const double rinv = rsqrt_f64(r2), r = r2 * rinv, rinv2 = rinv * rinv;
+  if (s.periodic) ewald_coeffs_f64<4>(r, rinv, rinv2, s.beta, c);
+  else bare_coeffs<double, 4>(rinv, rinv2, c);
+  c[5] = 0.0;
+  const double m = Mj.d[0] * Rv[0] + Mj.d[1] * Rv[1] + Mj.d[2] * Rv[2];
+  double t[3];
+  tvec(Mj.t, Rv, t);
+  const double n = (1.0 / 3.0) * (t[0] * Rv[0] + t[1] * Rv[1] + t[2] * Rv[2]);
+  PotTerms T;
+  pot_terms<2>(c, Mj, m, t, n, T);
+  phi += fma(n, c[2], fma(m, c[1], Mj.q * c[0]));
+  pot_add<2>(T, Mj.t, Rv, P);
+  const double sj = rec.d.w;
+  if (near && si > 0.0 && sj > 0.0) {
+    const double x = thole_a_pair(s, i, j) * r2 * r * si * sj;
+    if (x < 50.0) {
+      double tp[5], c0[4], E[3];
+      thole_tp_f64(x, tp);
+      bare_coeffs<double, 3>(rinv, rinv2, c0);
+#pragma unroll
+      for (int n = 1; n <= 3; ++n) c[n] = tp[n] * c0[n];
+      mp_field<double>(c, Mj, Rv, E);
+      acc[0] -= E[0]; acc[1] -= E[1]; acc[2] -= E[2];
+    }
+  }
+}
+
 // Intermolecular pairs within the cutoff (precision R): MM energy partials
 // (S_EREAL) and the damped field added to E0 of polarizable sites.  Near
 // entries first, then far ones (no damping).
@@ -231,17 +289,38 @@ __global__ __launch_bounds__(kBlock) void k_perm(SysView s, Reduce red, double4*
     const R si = site_s<R>(s, i);
     const int* row = s.nb_all + (size_t)i * s.cap_all;
     const int nn = s.nc_near[i], nf = s.nc_all[i] - nn;
-    for (int k = sub; k < nn; k += G) perm_pair<R, true>(s, i, row[k], pi, Mi, xi, si, U, acc);
-    // far entries two per step (same summation order): the second pair's
-    // gathers are issued while the first is evaluated
     const int* far = row + s.cap_all - 1;
-    int k = sub;
-    for (; k + G < nf; k += 2 * G) {
-      const int j0 = far[-k], j1 = far[-(k + G)];
-      perm_pair<R, false>(s, i, j0, pi, Mi, xi, si, U, acc);
-      perm_pair<R, false>(s, i, j1, pi, Mi, xi, si, U, acc);
-    }
+    if constexpr (sizeof(R) == sizeof(double)) {
+      PotSums P = {};
+      double phi = 0.0;
+      const int cnt = nn + nf;
+      auto entry = [&](int k) { return list_entry(row, s.cap_all, nn, min(k, cnt - 1)); };
+      if (sub < cnt) {
+        int j = entry(sub), jn = entry(sub + G);
+        SiteRec next = site_rec(s, j);
+        for (int k = sub; k < cnt; k += G) {
+          const SiteRec rec = next;
+          const int jr = j;
+          j = jn;
+          next = site_rec(s, j);
+          jn = entry(k + 2 * G);
+          perm_pair_pot(s, i, jr, rec, k < nn, xi, si, phi, P, acc);
+        }
+      }
+      U = 0.5 * pot_energy(Mi, phi, P);
+      acc[0] -= P.e[0]; acc[1] -= P.e[1]; acc[2] -= P.e[2];
+    } else {
+      for (int k = sub; k < nn; k += G) perm_pair<R, true>(s, i, row[k], pi, Mi, xi, si, U, acc);
+      // far entries two per step (same summation order): the second pair's
+      // gathers are issued while the first is evaluated
+      int k = sub;
+      for (; k + G < nf; k += 2 * G) {
+        const int j0 = far[-k], j1 = far[-(k + G)];
+        perm_pair<R, false>(s, i, j0, pi, Mi, xi, si, U, acc);
+        perm_pair<R, false>(s, i, j1, pi, Mi, xi, si, U, acc);
+      }
     if (k < nf) perm_pair<R, false>(s, i, far[-k], pi, Mi, xi, si, U, acc);
+    }
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) acc[a] = group_sum<G>(acc[a]);
@@ -705,6 +784,60 @@ __device__ __forceinline__ void force_pair(const SysView& s, int i, int j, const
   }
 }
 
+// The same pair in FP64 without the virial, from summed potentials Phi.  With
+// D = B - cT the force on i is that of Phi_B(M'_j) - Phi_D(mu_j) on M'_i less
+// that of Phi_D(M_j) on mu_i, which needs only second derivatives: P and Q.
+__device__ __forceinline__ void force_pair_pot(const SysView& s, int i, int j, const SiteRec& rec,
+                                               const double4& mu, bool near, const double xi[3],
+                                               double si, PotSums& P, double Qg[6], double& Qs) {
+  MP<double> Mj;
+  double Rv[3], xj[3], c[6];
+  rec_mp(rec, Mj, xj);
+  Mj.d[0] += mu.x; Mj.d[1] += mu.y; Mj.d[2] += mu.z;
+  displacement<double>(s, xi, xj, Rv);
+  const double r2 = Rv[0] * Rv[0] + Rv[1] * Rv[1] + Rv[2] * Rv[2];
+  const double rinv = rsqrt_f64(r2), r = r2 * rinv, rinv2 = rinv * rinv;
+  if (s.periodic) ewald_coeffs_f64<5>(r, rinv, rinv2, s.beta, c);
+  else bare_coeffs<double, 5>(rinv, rinv2, c);
+  const double m = Mj.d[0] * Rv[0] + Mj.d[1] * Rv[1] + Mj.d[2] * Rv[2];
+  double t[3];
+  tvec(Mj.t, Rv, t);
+  const double n = (1.0 / 3.0) * (t[0] * Rv[0] + t[1] * Rv[1] + t[2] * Rv[2]);
+  PotTerms T;
+  pot_terms<3>(c, Mj, m, t, n, T);
+  const double sj = rec.d.w;
+  if (near && si > 0.0 && sj > 0.0) {
+    const double x = thole_a_pair(s, i, j) * r2 * r * si * sj;
+    if (x < 50.0) {
+      double D[6], c0[5];
+      thole_tp_f64(x, D);
+      bare_coeffs<double, 4>(rinv, rinv2, c0);
+#pragma unroll
+      for (int l = 1; l <= 4; ++l) D[l] *= c0[l];
+      const double u[3] = {mu.x, mu.y, mu.z};
+      const double mu_r = u[0] * Rv[0] + u[1] * Rv[1] + u[2] * Rv[2];
+      T.S1 = fma(-mu_r, D[2], T.S1);
+      T.S2 = fma(-mu_r, D[3], T.S2);
+      T.S3 = fma(-mu_r, D[4], T.S3);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        T.W1[a] = fma(-D[1], u[a], T.W1[a]);
+        T.W2[a] = fma(-D[2], u[a], T.W2[a]);
+        T.W3[a] = fma(-D[3], u[a], T.W3[a]);
+        Mj.d[a] -= u[a];
+      }
+      PotTerms V;
+      pot_terms<2>(D, Mj, m - mu_r, t, n, V);
+      double y[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) y[a] = fma(0.5 * V.S2, Rv[a], -V.W2[a]);
+      sym_add(Rv, y, V.k2, Mj.t, Qg);
+      Qs += V.S1;
+    }
+  }
+  pot_add<3>(T, Mj.t, Rv, P);
+}
+
 // Intermolecular pairs within the cutoff (precision R); adds to Fout.
 // Near entries first (the damped ones are among them), then far ones.
 template <typename R, int G, bool VIR, bool FG>
@@ -728,17 +861,59 @@ __global__ __launch_bounds__(kBlock) void k_force(SysView s, Reduce red, const d
     const R si = site_s<R>(s, i);
     const int* row = s.nb_all + (size_t)i * s.cap_all;
     const int nn = s.nc_near[i], nf = s.nc_all[i] - nn;
-    for (int k = sub; k < nn; k += G)
-      force_pair<R, true, VIR, FG>(s, i, row[k], Mi, Pi, xi, si, mu, mu32, F, W, E, Gg);
     const int* far = row + s.cap_all - 1;
-    int k = sub;
-    for (; k + G < nf; k += 2 * G) {
-      const int j0 = far[-k], j1 = far[-(k + G)];
-      force_pair<R, false, VIR, FG>(s, i, j0, Mi, Pi, xi, si, mu, mu32, F, W, E, Gg);
-      force_pair<R, false, VIR, FG>(s, i, j1, Mi, Pi, xi, si, mu, mu32, F, W, E, Gg);
+    if constexpr (sizeof(R) == sizeof(double) && !VIR) {
+      PotSums P = {};
+      double Qg[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, Qs = 0.0;
+      const int cnt = nn + nf;
+      if (sub < cnt) {
+        // two records in turn: one is loaded while the other's pair is summed
+        auto entry = [&](int k) { return list_entry(row, s.cap_all, nn, min(k, cnt - 1)); };
+        auto pair = [&](int k, int j, const SiteRec& rec, const double4& m) {
+          force_pair_pot(s, i, j, rec, m, k < nn, xi, si, P, Qg, Qs);
+        };
+        int ja = entry(sub), jb = entry(sub + G);
+        SiteRec ra = site_rec(s, ja), rb;
+        double4 ma = mu[ja], mb;
+        for (int k = sub; k < cnt; k += 2 * G) {
+          rb = site_rec(s, jb);
+          mb = mu[jb];
+          const int j0 = ja, j1 = jb;
+          ja = entry(k + 2 * G);
+          pair(k, j0, ra, ma);
+          if (k + G >= cnt) break;
+          ra = site_rec(s, ja);
+          ma = mu[ja];
+          jb = entry(k + 3 * G);
+          pair(k + G, j1, rb, mb);
+        }
+      }
+      // the site's own multipoles again, not kept over the loop
+      load_mp<double>(s, i, Pi, xr);
+      Pi.d[0] += mui[0]; Pi.d[1] += mui[1]; Pi.d[2] += mui[2];
+      pot_force(Pi, P, F);
+      double qf[3];
+      tvec(Qg, mui, qf);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) F[a] += qf[a] - Qs * mui[a];
+      if (FG) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) E[a] -= P.e[a];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) Gg[k] -= P.g[k] - (k == 0 || k == 3 || k == 5 ? P.s1 : 0.0);
+      }
+    } else {
+      for (int k = sub; k < nn; k += G)
+        force_pair<R, true, VIR, FG>(s, i, row[k], Mi, Pi, xi, si, mu, mu32, F, W, E, Gg);
+      int k = sub;
+      for (; k + G < nf; k += 2 * G) {
+        const int j0 = far[-k], j1 = far[-(k + G)];
+        force_pair<R, false, VIR, FG>(s, i, j0, Mi, Pi, xi, si, mu, mu32, F, W, E, Gg);
+        force_pair<R, false, VIR, FG>(s, i, j1, Mi, Pi, xi, si, mu, mu32, F, W, E, Gg);
+      }
+      if (k < nf)
+        force_pair<R, false, VIR, FG>(s, i, far[-k], Mi, Pi, xi, si, mu, mu32, F, W, E, Gg);
     }
-    if (k < nf)
-      force_pair<R, false, VIR, FG>(s, i, far[-k], Mi, Pi, xi, si, mu, mu32, F, W, E, Gg);
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) F[a] = group_sum<G>(F[a]);

@@ -135,6 +135,74 @@ __device__ __forceinline__ void thole_tp(R x, R tp[5]) {
   tp[4] = (R(1) + x + R(18.0 / 35.0) * x2 + R(9.0 / 35.0) * x2 * x) * e;
 }
 
+// The same in FP64 for the kernels that evaluate every pair of a list
+// (about 300 FP64 instructions each, which is what bounds them): 2^k times a
+// polynomial of degree 11 for exp(-x^2), without the library's special cases
+// (the argument is finite and never positive; below -700 it is taken there,
+// 1e-304), and the erfcx series by Horner's rule, half Clenshaw's steps.
+// a b + c with the constant c in scalar registers: the compiler's own choice,
+// an add into a copy of c, keeps some 40 constants in 80 vector registers
+// over the pair loops: 256 registers, and one wavefront per SIMD, in the
+// force kernel.
+__device__ __forceinline__ double fma_const(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+__device__ __forceinline__ double exp_neg(double x) {
+  x = fmax(x, -700.0);
+  const double k = rint(x * 1.4426950408889634);
+  const double r = fma(k, -2.3190468138462996e-17, fma(k, -0.6931471805599453, x));
+  double q = kExpQ[kExpDeg];
+#pragma unroll
+  for (int m = kExpDeg - 1; m >= 0; --m) q = fma_const(q, r, kExpQ[m]);
+  return ldexp(fma(r * r, q, r) + 1.0, (int)k);
+}
+
+// 1 / sqrt(x): the hardware's estimate and one third-order step.
+__device__ __forceinline__ double rsqrt_f64(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+__device__ __forceinline__ double erfcx_horner(double x) {
+  x = fmin(x, kErfcxMax);
+  const double d = fma(kErfcxPF64, x, 1.0);
+  double t = (double)__builtin_amdgcn_rcpf((float)d);
+  t = t * fma(-d, t, 2.0);
+  t = t * fma(-d, t, 2.0);
+  const double u = fma(t - kErfcxT0F64, 2.0 / (1.0 - kErfcxT0F64), -1.0);
+  double b = kErfcxMF64[kErfcxDegF64];
+#pragma unroll
+  for (int k = kErfcxDegF64 - 1; k >= 0; --k) b = fma_const(b, u, kErfcxMF64[k]);
+  return b;
+}
+
+template <int N>
+__device__ __forceinline__ void ewald_coeffs_f64(double r, double rinv, double rinv2, double beta,
+                                                 double B[N + 1]) {
+  const double br = beta * r;
+  const double ex = exp_neg(-br * br);
+  B[0] = ex * erfcx_horner(br) * rinv;
+  const double t = 2.0 * beta * beta;
+  double h = ex * (t / (beta * kSqrtPi));
+#pragma unroll
+  for (int n = 1; n <= N; ++n) {
+    B[n] = fma(double(2 * n - 1), B[n - 1], h) * rinv2;
+    h *= t;
+  }
+}
+
+__device__ __forceinline__ void thole_tp_f64(double x, double tp[5]) {
+  const double e = exp_neg(-x);
+  tp[0] = 0.0;
+  tp[1] = e;
+  tp[2] = (1.0 + x) * e;
+  tp[3] = fma(x, fma(0.6, x, 1.0), 1.0) * e;
+  tp[4] = fma(x, fma(x, fma(9.0 / 35.0, x, 18.0 / 35.0), 1.0), 1.0) * e;
+}
+
 template <typename R>
 struct MP {
   R q;
@@ -206,6 +274,124 @@ __device__ __forceinline__ void mp_field(const R c[6], const MP<R>& B, const R R
   const R rad = B.q * c[1] + drj * c[2] + R(1.0 / 3.0) * qrrj * c[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) E[a] = Rv[a] * rad - (B.d[a] * c[1] + R(2.0 / 3.0) * qjr[a] * c[2]);
+}
+
+// Derivatives at r_i of the potential phi of multipoles at r_j, summed over
+// j: a site's multipoles meet the sums once instead of every pair.  With
+// S_k = q c_k + (d.R) c_{k+1} + 1/3 (R Theta R) c_{k+2} and
+// W_k = d c_k + 2/3 (Theta R) c_{k+1}, dS_k/dR_a = -R_a S_{k+1} + W_{k+1,a}, so
+//   phi            = S_0
+//   d_a phi        = -R_a S_1 + W_1a
+//   d_a d_b phi    = R_a y_b + R_b y_a + 2/3 c_2 Theta_ab - delta_ab S_1,
+//                    y = R S_2 / 2 - W_2
+//   d_a d_b d_c phi = -(R_a u_bc + R_b u_ac + R_c u_ab) + delta_ab z_c + delta_ac z_b
+//                    + delta_bc z_a,  u_bc = R_b v_c + R_c v_b + 2/3 c_3 Theta_bc,
+//                    v = R S_3 / 6 - W_3 / 2,  z = R S_2 - W_2.
+// Site i's quadrupole is contracted over b, c with the terms in delta_bc left
+// out, as in mp_pair (they meet its trace, which is zero).  The FP64 pair loops
+// are bound by their instructions: sums instead of pair energies and forces,
+// with the functions above, take 388 vector instructions per entry of the
+// force to 245 and 254 of the permanent field to 190; over 160,000 sites
+// (cutoff 9, 509 entries each) 1270 us became 810 and 950 became 610.
+struct PotSums {
+  double e[3];         // d_a phi
+  double g[6], s1;     // the second derivatives without their S_1; S_1
+  double z[3], k[10];  // z; R_a u_bc + ...: xxx yyy zzz (a third of them), xxy xxz yyx yyz zzx zzy, xyz
+};
+
+// A source's S_1..S_3, W_1..W_3 and, of its quadrupole, 2/3 c_2 and 2/3 c_3.
+struct PotTerms {
+  double S1, S2, S3, W1[3], W2[3], W3[3], k2, k3;
+};
+
+// R_a y_b + R_b y_a + k Theta_ab
+__device__ __forceinline__ void sym_add(const double R[3], const double y[3], double k,
+                                        const double t[6], double g[6]) {
+  g[0] = fma(2.0 * R[0], y[0], fma(k, t[0], g[0]));
+  g[1] = fma(R[0], y[1], fma(R[1], y[0], fma(k, t[1], g[1])));
+  g[2] = fma(R[0], y[2], fma(R[2], y[0], fma(k, t[2], g[2])));
+  g[3] = fma(2.0 * R[1], y[1], fma(k, t[3], g[3]));
+  g[4] = fma(R[1], y[2], fma(R[2], y[1], fma(k, t[4], g[4])));
+  g[5] = fma(2.0 * R[2], y[2], fma(k, t[5], g[5]));
+}
+
+// Terms of the first two (TOP 2) or three derivatives' sums; m = d.R,
+// t = Theta R, n = R Theta R / 3.
+template <int TOP>
+__device__ __forceinline__ void pot_terms(const double c[6], const MP<double>& M, double m,
+                                          const double t[3], double n, PotTerms& T) {
+  T.k2 = (2.0 / 3.0) * c[2];
+  T.k3 = (2.0 / 3.0) * c[3];
+  T.S1 = fma(n, c[3], fma(m, c[2], M.q * c[1]));
+  T.S2 = fma(n, c[4], fma(m, c[3], M.q * c[2]));
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    T.W1[a] = fma(c[1], M.d[a], T.k2 * t[a]);
+    T.W2[a] = fma(c[2], M.d[a], T.k3 * t[a]);
+  }
+  if (TOP == 3) {
+    const double k4 = (2.0 / 3.0) * c[4];
+    T.S3 = fma(n, c[5], fma(m, c[4], M.q * c[3]));
+#pragma unroll
+    for (int a = 0; a < 3; ++a) T.W3[a] = fma(c[3], M.d[a], k4 * t[a]);
+  }
+}
+
+template <int TOP>
+__device__ __forceinline__ void pot_add(const PotTerms& T, const double Th[6], const double R[3],
+                                        PotSums& P) {
+  const double h = 0.5 * T.S2;
+  double y[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    P.e[a] += fma(-T.S1, R[a], T.W1[a]);
+    y[a] = fma(h, R[a], -T.W2[a]);
+    if (TOP == 3) P.z[a] += fma(h, R[a], y[a]);
+  }
+  sym_add(R, y, T.k2, Th, P.g);
+  if (TOP == 3) {
+    P.s1 += T.S1;
+    const double s6 = (1.0 / 6.0) * T.S3;
+    double v[3], u[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) v[a] = fma(s6, R[a], -0.5 * T.W3[a]);
+    sym_add(R, v, T.k3, Th, u);
+    const double R2[3] = {2.0 * R[0], 2.0 * R[1], 2.0 * R[2]};
+    P.k[0] = fma(R[0], u[0], P.k[0]);
+    P.k[1] = fma(R[1], u[3], P.k[1]);
+    P.k[2] = fma(R[2], u[5], P.k[2]);
+    P.k[3] = fma(R2[0], u[1], fma(R[1], u[0], P.k[3]));
+    P.k[4] = fma(R2[0], u[2], fma(R[2], u[0], P.k[4]));
+    P.k[5] = fma(R2[1], u[1], fma(R[0], u[3], P.k[5]));
+    P.k[6] = fma(R2[1], u[4], fma(R[2], u[3], P.k[6]));
+    P.k[7] = fma(R2[2], u[2], fma(R[0], u[5], P.k[7]));
+    P.k[8] = fma(R2[2], u[4], fma(R[1], u[5], P.k[8]));
+    P.k[9] = fma(R[0], u[4], fma(R[1], u[2], fma(R[2], u[1], P.k[9])));
+  }
+}
+
+// Energy of multipoles A in the summed potential phi.
+__device__ __forceinline__ double pot_energy(const MP<double>& A, double phi, const PotSums& P) {
+  const double tg = A.t[0] * P.g[0] + A.t[3] * P.g[3] + A.t[5] * P.g[5] +
+                    2.0 * (A.t[1] * P.g[1] + A.t[2] * P.g[2] + A.t[4] * P.g[4]);
+  return A.q * phi + (A.d[0] * P.e[0] + A.d[1] * P.e[1] + A.d[2] * P.e[2]) + (1.0 / 3.0) * tg;
+}
+
+// Force on multipoles A in the summed potential.
+__device__ __forceinline__ void pot_force(const MP<double>& A, const PotSums& P, double F[3]) {
+  double dg[3], tz[3];
+  tvec(P.g, A.d, dg);
+  tvec(A.t, P.z, tz);
+  const double tk[3] = {
+      3.0 * A.t[0] * P.k[0] + A.t[3] * P.k[5] + A.t[5] * P.k[7] +
+          2.0 * (A.t[1] * P.k[3] + A.t[2] * P.k[4] + A.t[4] * P.k[9]),
+      A.t[0] * P.k[3] + 3.0 * A.t[3] * P.k[1] + A.t[5] * P.k[8] +
+          2.0 * (A.t[1] * P.k[5] + A.t[2] * P.k[9] + A.t[4] * P.k[6]),
+      A.t[0] * P.k[4] + A.t[3] * P.k[6] + 3.0 * A.t[5] * P.k[2] +
+          2.0 * (A.t[1] * P.k[9] + A.t[2] * P.k[7] + A.t[4] * P.k[8])};
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    F[a] += -A.q * P.e[a] - dg[a] + P.s1 * A.d[a] + (1.0 / 3.0) * tk[a] - (2.0 / 3.0) * tz[a];
 }
 
 // Field at r_i of a point dipole p at r_j (coefficients c1, c2).
