@@ -565,8 +565,9 @@ void launch_pol_extents(const RecArgs& a, double* out, hipStream_t s) {
 // One wavefront builds the rows of one slice of a cell's sites: the cell's
 // sites are dealt to `slices` wavefronts in contiguous runs (launch_nlist's
 // caller picks the count, nlist_slices), and lists and their order do not
-// depend on it.  Bound by vector issue where the wavefronts fill the SIMDs
-// (0.42 of the issue peak at 32,000 waters) and by the length of one
+// depend on it.  Bound by instruction issue where the wavefronts fill the
+// SIMDs (0.6 of the vector issue peak at 32,000 waters: 486 us, against 645
+// with a branch per chunk and the chunks loaded in turn) and by the length of one
 // wavefront's chain of candidate chunks where they do not: with one
 // wavefront per cell the build took 300 us at 4,096 waters, 770 us at 1,001
 // and 1.3 ms for a cluster of 80 (one cell), and whole evaluations went
@@ -584,7 +585,9 @@ void launch_pol_extents(const RecArgs& a, double* out, hipStream_t s) {
 //  * each i-site's five running counts live in lane t and are read once per
 //    pass over those chunks into wave-uniform (scalar) registers, so a
 //    candidate chunk costs the distance test, the lane masks and the slot
-//    arithmetic of its hits; hits are compacted in lane order;
+//    arithmetic of its hits, about 36 instructions without a branch (the few
+//    passes that hold the site's own molecule take one); hits are compacted
+//    in lane order;
 //  * the slice's count maxima go to its own slot of cellmax (plain stores;
 //    launch_cellmax_reduce folds them), not to one atomic per wavefront on
 //    four shared addresses.
@@ -605,7 +608,7 @@ __device__ __forceinline__ unsigned long long mask_eq(int a, int b) {
 template <bool NI>
 __global__ __launch_bounds__(64) void k_nlist(NlistArgs a) {
   __shared__ double xi[kNlIB], yi[kNlIB], zi[kNlIB];
-  __shared__ int run_s[50], run_off[51], run_code[50];
+  __shared__ int run_s[50], run_off[64], run_code[50];
   const int lane = threadIdx.x;
   const int cell = blockIdx.x / a.slices, slice = blockIdx.x - cell * a.slices;
   const int nc0 = a.nc[0], nc1 = a.nc[1], nc2 = a.nc[2];
@@ -645,7 +648,7 @@ __global__ __launch_bounds__(64) void k_nlist(NlistArgs a) {
     else if (x0 >= 0 && x1 < nc0) { f0 = x0; l0 = x1; k0 = 1; }
     else if (x0 < 0) { f0 = 0; l0 = x1; k0 = 1; f1 = nc0 + x0; l1 = nc0 - 1; k1 = 0; }
     else { f0 = x0; l0 = nc0 - 1; k0 = 1; f1 = 0; l1 = x1 - nc0; k1 = 2; }
-    const int yzc = 3 * yc + 9 * zc;
+    const int yzc = 4 * yc + 16 * zc;
     run_s[2 * lane] = a.cell_start[row + f0];
     len0 = a.cell_start[row + l0 + 1] - a.cell_start[row + f0];
     run_code[2 * lane] = k0 + yzc;
@@ -668,9 +671,10 @@ __global__ __launch_bounds__(64) void k_nlist(NlistArgs a) {
       run_off[2 * lane + 2] = x;
     }
     if (lane == 0) run_off[0] = 0;
+    if (lane > 50) run_off[lane] = INT_MAX;
   }
   __syncthreads();
-  const int ncand = run_off[50], nrun = 2 * sy * sz;
+  const int ncand = run_off[50];
   const unsigned cap_all = a.cap_all;
   const int cap_in = a.cap_in, cap_pol = a.cap_pol, cap_ipol = a.cap_ipol;
   const double cut2 = a.cutoff2, split2 = a.rsplit2;
@@ -687,6 +691,9 @@ __global__ __launch_bounds__(64) void k_nlist(NlistArgs a) {
       pol_v = a.polidx[ib + lane];
     }
     __syncthreads();
+    // index of the pass's first polarizable site
+    const unsigned long long pols = __builtin_amdgcn_sicmp(pol_v, 0, kCmpSGE);
+    const int pol0 = pols ? rl(pol_v, __builtin_ctzll(pols)) : 0;
     // counts of i-site `lane`: all near (cnt0) and far (cntf), in, pol, ipol
     int cnt0 = 0, cntf = 0, cnt1 = 0, cnt2 = 0, cnt3 = 0;
     for (int c = 0; c < ncand; c += 64 * kNlG) {
@@ -695,41 +702,48 @@ __global__ __launch_bounds__(64) void k_nlist(NlistArgs a) {
       double xj[kNlG], yj[kNlG], zj[kNlG];
       int jj[kNlG], molj[kNlG], polj[kNlG];
       unsigned long long pjm[kNlG];
+      // the chunks' searches (last run that starts at or before the
+      // candidate) and loads side by side, without branches: one after the
+      // other they were a third of a wavefront's time
+      int run[kNlG];
+      double4 pj[kNlG];
+#pragma unroll
+      for (int g = 0; g < kNlG; ++g) run[g] = 0;
+#pragma unroll
+      for (int step = 32; step; step >>= 1)
+#pragma unroll
+        for (int g = 0; g < kNlG; ++g)
+          if (run_off[run[g] + step] <= c + g * 64 + lane) run[g] += step;
 #pragma unroll
       for (int g = 0; g < kNlG; ++g) {
         const int cidx = c + g * 64 + lane;
-        xj[g] = yj[g] = zj[g] = INFINITY;
-        jj[g] = -1; molj[g] = -1; polj[g] = -1;
-        if (cidx < ncand) {
-          int lo = 0, hi = nrun;
-          while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (run_off[mid] <= cidx) lo = mid; else hi = mid;
-          }
-          const int j = run_s[lo] + (cidx - run_off[lo]);
-          const int code = run_code[lo];
-          const double4 p = a.sp[j];
-          xj[g] = p.x + L0 * (double)(code % 3 - 1);
-          yj[g] = p.y + L1 * (double)((code / 3) % 3 - 1);
-          zj[g] = p.z + L2 * (double)(code / 9 - 1);
-          jj[g] = j;
-          molj[g] = a.mol_s[j];
-          polj[g] = a.polidx[j];
-        }
+        run[g] = cidx < ncand ? run[g] : 0;
+        jj[g] = cidx < ncand ? run_s[run[g]] + (cidx - run_off[run[g]]) : 0;
+        pj[g] = a.sp[jj[g]];
+        molj[g] = a.mol_s[jj[g]];
+        polj[g] = a.polidx[jj[g]];
+      }
+#pragma unroll
+      for (int g = 0; g < kNlG; ++g) {
+        const bool on = c + g * 64 + lane < ncand;
+        const int code = run_code[run[g]];
+        xj[g] = on ? pj[g].x + L0 * (double)((code & 3) - 1) : (double)INFINITY;
+        yj[g] = on ? pj[g].y + L1 * (double)(((code >> 2) & 3) - 1) : (double)INFINITY;
+        zj[g] = on ? pj[g].z + L2 * (double)((code >> 4) - 1) : (double)INFINITY;
+        jj[g] = on ? jj[g] : -1;
+        molj[g] = on ? molj[g] : -1;
+        polj[g] = on ? polj[g] : -1;
         pjm[g] = __builtin_amdgcn_sicmp(polj[g], 0, kCmpSGE);
       }
+      // rows of the sites in turn: consecutive, as polarizable indices are
+      int* row_all = a.nb_all + (size_t)ib * cap_all;
+      int* row_pol = a.nb_pol + (size_t)pol0 * cap_pol;
       for (int t = 0; t < ni; ++t) {
         const double x = xi[t], y = yi[t], z = zi[t];
-        const int i = ib + t;
-        const int mi = rl(mol_v, t), pi_ = rl(pol_v, t);
-        // site t's counts, wave-uniform for the chunks of this pass; a
-        // lane's slot is the count plus the lower lanes of its mask
-        int k0 = rl(cnt0, t), kf = rl(cntf, t), k1 = rl(cnt1, t), k2 = rl(cnt2, t),
-            k3 = rl(cnt3, t);
-        int* row_all = a.nb_all + (size_t)i * cap_all;
-        int* row_in = a.nb_in + (size_t)i * cap_in;
-        int* row_pol = a.nb_pol + (size_t)(pi_ >= 0 ? pi_ : 0) * cap_pol;
-        int* row_ipol = a.nb_ipol + (size_t)(pi_ >= 0 ? pi_ : 0) * cap_ipol;
+        const int mi = rl(mol_v, t);
+        // lane masks of every chunk before any of them is used, straight
+        // line: cut (intermolecular within the cutoff), near of them, mol
+        unsigned long long cut[kNlG], near[kNlG], mol[kNlG], any = 0ull;
 #pragma unroll
         for (int g = 0; g < kNlG; ++g) {
           double dx = x - xj[g], dy = y - yj[g], dz = z - zj[g];
@@ -739,57 +753,61 @@ __global__ __launch_bounds__(64) void k_nlist(NlistArgs a) {
             dz -= W2 * rint(dz * iW2);
           }
           const double r2 = dx * dx + dy * dy + dz * dz;
-          // the same compares give the wave's masks and each lane's own
-          // bit (the compiler folds them into one instruction each)
-          const bool in_cut = r2 < cut2, in_mol = molj[g] == mi, in_near = r2 < split2;
-          const unsigned long long bmol = mask_eq(molj[g], mi);
-          const unsigned long long b0 = mask_lt(r2, cut2) & ~bmol;   // intermolecular
-          if ((b0 | bmol) == 0ull) continue;   // no neighbour of site t in this chunk
-          const bool inter = in_cut && !in_mol;
-          const bool same = in_mol && jj[g] != i;
-          unsigned long long b1 = 0ull;        // same molecule, not site t itself
-          if (bmol) b1 = bmol & ~mask_eq(jj[g], i);
-          if (b0) {
-            // near entries from the front of the row, far ones from its
-            // back, in one store
-            const unsigned long long bnear = mask_lt(r2, split2);
-            const unsigned long long bn = b0 & bnear, bf = b0 & ~bnear;
-            if (inter) {
-              const int kn = lanes_below(bn, k0), kb = lanes_below(bf, kf);
-              const unsigned k = in_near ? (unsigned)kn : cap_all - 1u - (unsigned)kb;
-              if (k < cap_all) row_all[k] = jj[g];
-            }
-            k0 += __popcll(bn);
-            kf += __popcll(bf);
+          mol[g] = mask_eq(molj[g], mi);
+          cut[g] = mask_lt(r2, cut2) & ~mol[g];
+          near[g] = mask_lt(r2, split2) & cut[g];
+          any |= mol[g];
+        }
+        const bool pol = rl(pol_v, t) >= 0;
+        // site t's counts, wave-uniform for the chunks of this pass; a
+        // lane's slot is the count plus the lower lanes of its mask; near
+        // entries from the front of the row, far ones from its back
+        int k0 = rl(cnt0, t), kf = rl(cntf, t);
+#pragma unroll
+        for (int g = 0; g < kNlG; ++g) {
+          const unsigned long long far = cut[g] & ~near[g];
+          const int kn = lanes_below(near[g], k0), kb = lanes_below(far, kf);
+          const unsigned k = __builtin_amdgcn_inverse_ballot_w64(near[g])
+                                 ? (unsigned)kn : cap_all - 1u - (unsigned)kb;
+          if (__builtin_amdgcn_inverse_ballot_w64(cut[g]) && k < cap_all) row_all[k] = jj[g];
+          k0 += __popcll(near[g]);
+          kf += __popcll(far);
+        }
+        const bool me = lane == t;
+        cnt0 = me ? k0 : cnt0;
+        cntf = me ? kf : cntf;
+        if (pol) {
+          int k2 = rl(cnt2, t);
+#pragma unroll
+          for (int g = 0; g < kNlG; ++g) {
+            const unsigned long long m = cut[g] & pjm[g];
+            const int k = lanes_below(m, k2);
+            if (__builtin_amdgcn_inverse_ballot_w64(m) && k < cap_pol) row_pol[(unsigned)k] = polj[g];
+            k2 += __popcll(m);
           }
-          if (b1) {
-            if (same) {
-              const int k = lanes_below(b1, k1);
-              if (k < cap_in) row_in[(unsigned)k] = jj[g];
-            }
+          cnt2 = me ? k2 : cnt2;
+        }
+        if (any) {   // same molecule, not site t itself
+          const int i = ib + t;
+          int k1 = rl(cnt1, t), k3 = rl(cnt3, t);
+          int* row_in = a.nb_in + (size_t)i * cap_in;
+          int* row_ipol = a.nb_ipol + (size_t)(pol ? rl(pol_v, t) : 0) * cap_ipol;
+#pragma unroll
+          for (int g = 0; g < kNlG; ++g) {
+            const unsigned long long b1 = mol[g] & ~mask_eq(jj[g], i);
+            const unsigned long long b3 = pol ? b1 & pjm[g] : 0ull;
+            const int k = lanes_below(b1, k1), kp = lanes_below(b3, k3);
+            if (__builtin_amdgcn_inverse_ballot_w64(b1) && k < cap_in) row_in[(unsigned)k] = jj[g];
+            if (__builtin_amdgcn_inverse_ballot_w64(b3) && kp < cap_ipol)
+              row_ipol[(unsigned)kp] = polj[g];
             k1 += __popcll(b1);
+            k3 += __popcll(b3);
           }
-          if (pi_ >= 0) {
-            const unsigned long long b2 = b0 & pjm[g], b3 = b1 & pjm[g];
-            if (b2) {
-              if (inter && polj[g] >= 0) {
-                const int k = lanes_below(b2, k2);
-                if (k < cap_pol) row_pol[(unsigned)k] = polj[g];
-              }
-              k2 += __popcll(b2);
-            }
-            if (b3) {
-              if (same && polj[g] >= 0) {
-                const int k = lanes_below(b3, k3);
-                if (k < cap_ipol) row_ipol[(unsigned)k] = polj[g];
-              }
-              k3 += __popcll(b3);
-            }
-          }
+          cnt1 = me ? k1 : cnt1;
+          cnt3 = me ? k3 : cnt3;
         }
-        if (lane == t) {
-          cnt0 = k0; cntf = kf; cnt1 = k1; cnt2 = k2; cnt3 = k3;
-        }
+        row_all += cap_all;
+        if (pol) row_pol += cap_pol;
       }
     }
     if (lane < ni) {
@@ -838,10 +856,12 @@ void launch_cellmax_reduce(const int4* cellmax, int count, int* out, hipStream_t
 }
 
 // Wavefronts per cell: enough for kNlWaves in all, at most one per site of
-// an average cell.
+// an average cell; two up to twice kNlWaves cells, where one each are too few
+// rounds of the 5,120 that fit to even out (9,261 cells: 546 against 486 us;
+// three take 520, as every slice loads the cell's candidates).
 int nlist_slices(int n, int ncell) {
   const int per_cell = (n + ncell - 1) / ncell;
-  return std::max(1, std::min(per_cell, kNlWaves / ncell));
+  return std::max(1, std::min(per_cell, std::max(kNlWaves / ncell, ncell < 2 * kNlWaves ? 2 : 1)));
 }
 
 void launch_nlist(const NlistArgs& a, int ncell, hipStream_t s) {
