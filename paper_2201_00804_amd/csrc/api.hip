@@ -1549,13 +1549,15 @@ sibfa_status setup_pme(sibfa_ctx c) {
   }
   const size_t nr = (size_t)pm.K[0] * pm.K[1] * pm.K[2];
   const size_t nh = (size_t)pm.kxh * pm.K[1] * pm.K[2];
+  pm.prow = pm.K[0] + order - 1;
+  const size_t np = (size_t)pm.prow * pm.K[1] * pm.K[2];
   double *Q, *phi, *G;
   double2* C;
   float *Q32, *phi32, *G32;
   float2* C32;
-  if (!alloc_into(c, c->pmebufs, Q, nr) || !alloc_into(c, c->pmebufs, phi, nr) ||
+  if (!alloc_into(c, c->pmebufs, Q, nr) || !alloc_into(c, c->pmebufs, phi, np) ||
       !alloc_into(c, c->pmebufs, C, nh) || !alloc_into(c, c->pmebufs, G, nh) ||
-      !alloc_into(c, c->pmebufs, Q32, nr) || !alloc_into(c, c->pmebufs, phi32, nr) ||
+      !alloc_into(c, c->pmebufs, Q32, nr) || !alloc_into(c, c->pmebufs, phi32, np) ||
       !alloc_into(c, c->pmebufs, C32, nh) || !alloc_into(c, c->pmebufs, G32, nh) ||
       !alloc_into(c, c->pmebufs, pm.tiles, (size_t)c->nbricks * pm.tile_size) ||
       !alloc_into(c, c->pmebufs, pm.tiles32, (size_t)c->nbricks * pm.tile_size))
@@ -1721,7 +1723,8 @@ size_t sibfa_footprint_bytes(int n_sites, int n_polarizable, const double* box,
     cap_pol = std::min(np, (size_t)(1.3 * np / V * sph) + 64);
     const size_t nr = (size_t)p->grid[0] * p->grid[1] * p->grid[2];
     const size_t nh = (size_t)(p->grid[0] / 2 + 1) * p->grid[1] * p->grid[2];
-    bytes += nr * 2 * (8 + 4) + nh * (16 + 8 + 8 + 4);
+    bytes += (nr * 2 + (size_t)(p->order - 1) * p->grid[1] * p->grid[2]) * (8 + 4) +
+             nh * (16 + 8 + 8 + 4);
     size_t tiles = 1;
     int edge[3];
     brick_edges(*p, edge);
@@ -1838,6 +1841,7 @@ sibfa_status sibfa_set_system(sibfa_ctx c, int n_sites, const double* xyz, const
   c->red = Reduce{};
   c->red.partials = partials;
   c->red.max_blocks = max_blocks;
+  c->red.wave_slot = -1;
   launch_fill_double(partials, 0.0, (size_t)S_COUNT * max_blocks, c->stream);
   launch_fill_int(c->is_pol + n, 0, 1, c->stream);
   HIP_TRY(hipMemcpyAsync(c->xyz_c, xyz, 3 * n * sizeof(double), hipMemcpyDeviceToDevice, c->stream));

@@ -99,7 +99,10 @@ struct PmeView {
   int kxh;             // K[0]/2 + 1
   double scale[3];     // K_a / L_a
   double* Q;           // real spread grid [K2][K1][K0] (x fastest)
-  double* phi;         // real potential grid, same layout
+  // real potential grid [K2][K1][prow]: a row repeats its first order - 1
+  // points after its last, so that a site's points of a row are consecutive
+  double* phi;
+  int prow;
   double2* C;          // complex half grid [K2][K1][kxh]
   float* Q32;
   float* phi32;
@@ -202,6 +205,7 @@ struct Reduce {
   double* partials;      // [S_COUNT][max_blocks]
   int max_blocks;
   int nparts[S_COUNT];
+  int wave_slot;         // the slot whose partials are of wavefronts, or -1
   const int* stop;       // solver iterations: kernels return at once when *stop != 0
 };
 
@@ -314,22 +318,85 @@ __device__ __forceinline__ void block_partial(double v, const Reduce& red, int s
   __syncthreads();
 }
 
-// Total of a slot written by an earlier kernel, returned to every thread.
-// Every thread of the block must call it.
-__device__ __forceinline__ double slot_total(const Reduce& red, int slot) {
-  __shared__ double sh[kBlock / 64];
-  const int n = red.nparts[slot];
+// This thread's share of a slot's partials, in index order; partials of
+// wavefronts (wave_slot) first add up to those of the blocks of kBlock threads
+// that they stand for, in block_partial's order.
+__device__ __forceinline__ double slot_share(const Reduce& red, int slot, int n) {
+  const double* p = red.partials + (size_t)slot * red.max_blocks;
   double v = 0.0;
-  for (int b = threadIdx.x; b < n; b += blockDim.x)
-    v += red.partials[(size_t)slot * red.max_blocks + b];
-  v = wave_sum(v);
+  if (slot == red.wave_slot) {
+    constexpr int W = kBlock / 64;
+    for (int b = threadIdx.x * W; b < n; b += blockDim.x * W) {
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < W; ++w) s += b + w < n ? p[b + w] : 0.0;
+      v += s;
+    }
+  } else {
+    for (int b = threadIdx.x; b < n; b += blockDim.x) v += p[b];
+  }
+  return v;
+}
+
+// Totals of slots written by earlier kernels, returned to every thread, read
+// and reduced side by side (one after the other each costs its own memory
+// latency and barriers).  Every thread of the block must call it.
+template <int N>
+__device__ __forceinline__ void slot_totals(const Reduce& red, const int (&slot)[N],
+                                            double (&out)[N]) {
+  __shared__ double sh[N][kBlock / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) sh[wid] = v;
+  double v[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = slot_share(red, slot[k], red.nparts[slot[k]]);
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    v[k] = wave_sum(v[k]);
+    if (lane == 0) sh[k][wid] = v[k];
+  }
   __syncthreads();
-  double s = 0.0;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += sh[w];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    double s = 0.0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += sh[k][w];
+    out[k] = s;
+  }
   __syncthreads();
-  return s;
+}
+__device__ __forceinline__ double slot_total(const Reduce& red, int slot) {
+  double t[1];
+  slot_totals<1>(red, {slot}, t);
+  return t[0];
+}
+
+// A site's P rows of P potential values in a plane, rows and values from the
+// base index down.  Each row is read as one run of values (at one load per
+// value the gathers of 64 sites keep the texture path busy, a cycle per cache
+// line and load), and all rows are on their way before the first is used,
+// which the scheduler would not do by itself.
+template <typename R, int P>
+struct GridRow {
+  R q[P];
+  __device__ __forceinline__ R operator[](int tx) const { return q[P - 1 - tx]; }
+};
+template <typename R, int P>
+__device__ __forceinline__ void grid_rows(const PmeView& pm, const int base[3], int tz,
+                                          GridRow<R, P> row[P]) {
+  const R* phi;
+  if constexpr (sizeof(R) == sizeof(double)) phi = pm.phi;
+  else phi = pm.phi32;
+  int iz = base[2] - tz;
+  if (iz < 0) iz += pm.K[2];
+  int ix = base[0] - (P - 1);
+  if (ix < 0) ix += pm.K[0];
+#pragma unroll
+  for (int ty = 0; ty < P; ++ty) {
+    int iy = base[1] - ty;
+    if (iy < 0) iy += pm.K[1];
+    row[ty] = *reinterpret_cast<const GridRow<R, P>*>(
+        phi + ((size_t)iz * pm.K[1] + iy) * pm.prow + ix);
+  }
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 template <typename R>

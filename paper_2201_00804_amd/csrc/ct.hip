@@ -352,15 +352,14 @@ __global__ __launch_bounds__(kBlock) void k_ct_gather_pot(SysView s, PmeView pm,
   site_splines<double, P, 1>(pm, x.x, x.y, x.z, base, th);
   double phi = 0.0, g[3] = {0.0, 0.0, 0.0};
   for (int tz = 0; tz < P; ++tz) {
-    int iz = base[2] - tz; if (iz < 0) iz += pm.K[2];
+    GridRow<double, P> row[P];
+    grid_rows<double, P>(pm, base, tz, row);
+#pragma unroll
     for (int ty = 0; ty < P; ++ty) {
-      int iy = base[1] - ty; if (iy < 0) iy += pm.K[1];
-      const size_t row = ((size_t)iz * pm.K[1] + iy) * pm.K[0];
       double s0 = 0.0, s1 = 0.0;
 #pragma unroll
       for (int tx = 0; tx < P; ++tx) {
-        int ix = base[0] - tx; if (ix < 0) ix += pm.K[0];
-        const double v = pm.phi[row + ix];
+        const double v = row[ty][tx];
         s0 += v * th[0][0][tx];
         s1 += v * th[0][1][tx];
       }

@@ -407,8 +407,13 @@ __global__ __launch_bounds__(kBlock) void k_fft_x_c2r(PmeView pm, int nl) {
   const cplx<T>* tw = stage_twiddles<T, kBlock>(gTw<T>(pm, 0), b + nl * ls, N);
   cplx<T>* res = lds_fft<T, kBlock>(a, b, N, nl, ls, pm.radcode[0], pm.nrad[0], tw, T(1));
   T* phi = gPhi<T>(pm);
+  const int rs = pm.prow, rep = pm.order - 1;
   for2d<kBlock>(nl, N, [&](int l, int x) {
-    if (l < rows) phi[(size_t)(row0 + l) * N + x] = res[l * ls + x].x;
+    if (l >= rows) return;
+    T* row = phi + (size_t)(row0 + l) * rs;
+    const T v = res[l * ls + x].x;
+    row[x] = v;
+    if (x < rep) row[N + x] = v;
   });
 }
 
@@ -501,11 +506,17 @@ __global__ __launch_bounds__(NT) void k_fft_plane_inv(PmeView pm) {
     rows[m * rs + k] = v;
   });
   cplx<T>* res = lds_fft<T, NT>(rows, cols, K0, K1 / 2, rs, pm.radcode[0], pm.nrad[0], tw0, T(1));
-  T* phi = gPhi<T>(pm) + (size_t)z * K1 * K0;
+  const int pr = pm.prow, rep = pm.order - 1;
+  T* phi = gPhi<T>(pm) + (size_t)z * K1 * pr;
   for2d<NT>(K1 / 2, K0, [&](int m, int x) {
     const cplx<T> v = res[m * rs + x];
-    phi[(2 * m) * K0 + x] = v.x;
-    phi[(2 * m + 1) * K0 + x] = v.y;
+    T* row = phi + (2 * m) * pr;
+    row[x] = v.x;
+    row[pr + x] = v.y;
+    if (x < rep) {
+      row[K0 + x] = v.x;
+      row[pr + K0 + x] = v.y;
+    }
   });
 }
 

@@ -359,13 +359,6 @@ __device__ __forceinline__ void load_pp<float>(const SysView& s, int j, float x[
   x[0] = a.x; x[1] = a.y; x[2] = a.z; sj = a.w;
 }
 
-template <typename R>
-__device__ __forceinline__ R grid_at(const PmeView& pm, size_t idx);
-template <>
-__device__ __forceinline__ double grid_at<double>(const PmeView& pm, size_t idx) { return pm.phi[idx]; }
-template <>
-__device__ __forceinline__ float grid_at<float>(const PmeView& pm, size_t idx) { return pm.phi32[idx]; }
-
 // Damped, screened dipole-dipole coefficients of the intermolecular pol
 // pairs, c1 = E_1 - P_1 e^-x c0_1 and c2 = E_2 - P_2 e^-x c0_2, in the
 // ELL layout of the pol list.  Positions are fixed during a solve, so the
@@ -547,15 +540,14 @@ __global__ __launch_bounds__(kBlock) void k_matvec_recip(SysView s, PmeView pm, 
     }
     double g[3] = {0.0, 0.0, 0.0};
     for (int tz = 0; tz < P; ++tz) {
-      int iz = base[2] - tz; if (iz < 0) iz += pm.K[2];
+      GridRow<R, P> row[P];
+      grid_rows<R, P>(pm, base, tz, row);
+#pragma unroll
       for (int ty = 0; ty < P; ++ty) {
-        int iy = base[1] - ty; if (iy < 0) iy += pm.K[1];
-        const size_t rowi = ((size_t)iz * pm.K[1] + iy) * pm.K[0];
         R s0 = 0, s1 = 0;
 #pragma unroll
         for (int tx = 0; tx < P; ++tx) {
-          int ix = base[0] - tx; if (ix < 0) ix += pm.K[0];
-          const R v = grid_at<R>(pm, rowi + ix);
+          const R v = row[ty][tx];
           s0 += v * th[0][0][tx];
           s1 += v * th[0][1][tx];
         }
@@ -1012,16 +1004,26 @@ void launch_matvec_real(const SysView& s, Reduce& red, const double4* p, const f
     hipExtLaunchKernelGGL((k_matvec<double, kG>), g, b, 0, st, t0, end, 0, s, red, p, p32, out,
                           dot_slot);
   if (t1 && done) (void)hipEventRecord(done, st);
-  if (!s.periodic && dot_slot >= 0) red.nparts[dot_slot] = (int)g.x;
+  if (!s.periodic && dot_slot >= 0) {
+    red.nparts[dot_slot] = (int)g.x;
+    red.wave_slot = -1;
+  }
 }
 
 template <int P>
 static void matvec_recip_p(const SysView& s, const PmeView& pm, Reduce& red, const double4* p,
                            double4* out, int dot_slot, bool mixed, hipStream_t st) {
-  const dim3 g((s.npol + kBlock - 1) / kBlock), b(kBlock);
+  // one wavefront per workgroup while four leave CUs idle: the texture path
+  // of each bounds its share (12,288 sites: 11.3 us with single loads and four,
+  // 5.6 us; with 96,000 sites rows and loads ahead alone 21.4 against 10.1)
+  const bool few = s.npol <= 256 * kBlock;
+  const dim3 b(few ? 64 : kBlock), g((s.npol + b.x - 1) / b.x);
   if (mixed) hipLaunchKernelGGL((k_matvec_recip<float, P>), g, b, 0, st, s, pm, red, p, out, dot_slot);
   else hipLaunchKernelGGL((k_matvec_recip<double, P>), g, b, 0, st, s, pm, red, p, out, dot_slot);
-  if (dot_slot >= 0) red.nparts[dot_slot] = (int)g.x;
+  if (dot_slot >= 0) {
+    red.nparts[dot_slot] = (int)g.x;
+    red.wave_slot = few ? dot_slot : -1;
+  }
 }
 
 void launch_matvec_recip(const SysView& s, const PmeView& pm, Reduce& red, const double4* p,

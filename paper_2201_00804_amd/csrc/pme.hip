@@ -15,13 +15,6 @@
 
 namespace sibfa {
 
-template <typename R>
-__device__ __forceinline__ R grid_phi(const PmeView& pm, size_t idx);
-template <>
-__device__ __forceinline__ double grid_phi<double>(const PmeView& pm, size_t idx) { return pm.phi[idx]; }
-template <>
-__device__ __forceinline__ float grid_phi<float>(const PmeView& pm, size_t idx) { return pm.phi32[idx]; }
-
 // ------------------------------------------------------------ spreading
 // Sites are binned by home brick, the brick of B^3 grid points (B <= 8, per
 // axis; the last brick along an axis never has fewer than p - 1 points)
@@ -340,15 +333,14 @@ __global__ __launch_bounds__(kBlock) void k_gather_field(SysView s, PmeView pm, 
   site_splines<R, P, 1>(pm, x.x, x.y, x.z, base, th);
   double g[3] = {0.0, 0.0, 0.0};
   for (int tz = 0; tz < P; ++tz) {
-    int iz = base[2] - tz; if (iz < 0) iz += pm.K[2];
+    GridRow<R, P> row[P];
+    grid_rows<R, P>(pm, base, tz, row);
+#pragma unroll
     for (int ty = 0; ty < P; ++ty) {
-      int iy = base[1] - ty; if (iy < 0) iy += pm.K[1];
-      const size_t row = ((size_t)iz * pm.K[1] + iy) * pm.K[0];
       R s0 = 0, s1 = 0;
 #pragma unroll
       for (int tx = 0; tx < P; ++tx) {
-        int ix = base[0] - tx; if (ix < 0) ix += pm.K[0];
-        const R v = grid_phi<R>(pm, row + ix);
+        const R v = row[ty][tx];
         s0 += v * th[0][0][tx];
         s1 += v * th[0][1][tx];
       }
@@ -390,16 +382,16 @@ __global__ __launch_bounds__(kBlock) void k_gather_force(SysView s, PmeView pm, 
     double D[64];
 #pragma unroll
     for (int k = 0; k < 64; ++k) D[k] = 0.0;
+#pragma unroll
     for (int tz = 0; tz < P; ++tz) {
-      int iz = base[2] - tz; if (iz < 0) iz += pm.K[2];
+      GridRow<R, P> row[P];
+      grid_rows<R, P>(pm, base, tz, row);
+#pragma unroll
       for (int ty = 0; ty < P; ++ty) {
-        int iy = base[1] - ty; if (iy < 0) iy += pm.K[1];
-        const size_t row = ((size_t)iz * pm.K[1] + iy) * pm.K[0];
         R sx[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int tx = 0; tx < P; ++tx) {
-          int ix = base[0] - tx; if (ix < 0) ix += pm.K[0];
-          const R v = grid_phi<R>(pm, row + ix);
+          const R v = row[ty][tx];
 #pragma unroll
           for (int k = 0; k < 4; ++k) sx[k] += v * th[0][k][tx];
         }
@@ -503,11 +495,16 @@ void launch_spread_dip(const SysView& s, const PmeView& pm, const double4* p, bo
   spread<false>(pm, s, p, mixed, st);
 }
 
+// Sites per workgroup of the gathers: one wavefront up to 65,536 sites (256
+// workgroups of four), so that few sites still spread over the CUs, whose
+// texture paths bound them.
+static dim3 gather_block(int n) { return dim3(n <= 256 * kBlock ? 64 : kBlock); }
+
 template <int P>
 static void gather_field_p(const SysView& s, const PmeView& pm, double4* E0, bool mixed,
                            hipStream_t st) {
   if (s.npol <= 0) return;
-  const dim3 g((s.npol + kBlock - 1) / kBlock), b(kBlock);
+  const dim3 b = gather_block(s.npol), g((s.npol + b.x - 1) / b.x);
   if (mixed) hipLaunchKernelGGL((k_gather_field<float, P>), g, b, 0, st, s, pm, E0);
   else hipLaunchKernelGGL((k_gather_field<double, P>), g, b, 0, st, s, pm, E0);
 }
@@ -525,7 +522,7 @@ template <int P, bool VIR>
 static void gather_force_pv(const SysView& s, const PmeView& pm, Reduce& red, const double4* mu,
                             const double4* Freal, const int* perm, double* out, bool mixed,
                             hipStream_t st, double4* FS, double* GS, bool self) {
-  const dim3 g((s.n + kBlock - 1) / kBlock), b(kBlock);
+  const dim3 b = gather_block(s.n), g((s.n + b.x - 1) / b.x);
   if (mixed)
     hipLaunchKernelGGL((k_gather_force<float, P, VIR>), g, b, 0, st, s, pm, red, mu, Freal, perm,
                        out, FS, GS, self);

@@ -292,8 +292,9 @@ __global__ __launch_bounds__(kBlock) void k_pc_update(SysView s, PcView pc, Redu
   if (stopped(red.stop)) return;
   const int pi = blockIdx.x * blockDim.x + threadIdx.x;
   double rz = 0.0, zz = 0.0;
-  const double rzt = slot_total(red, rz_slot);
-  const double gamma = rzt == 0.0 ? 0.0 : rzt / slot_total(red, S_PQ);
+  double tot[2];
+  slot_totals<2>(red, {rz_slot, S_PQ}, tot);
+  const double gamma = tot[0] == 0.0 ? 0.0 : tot[0] / tot[1];
   if (pi < s.npol) {
     switch (pc.n[pi]) {
       case 1: residual_group<1, false>(s, pc, pi, nullptr, q, gamma, x, p, r, z, nullptr, nullptr, rz, zz); break;

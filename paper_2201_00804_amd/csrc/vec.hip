@@ -48,8 +48,9 @@ __global__ __launch_bounds__(kBlock) void k_update(SysView s, Reduce red, int rz
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   double rz = 0.0, zz = 0.0;
   // r.z = 0 only for a zero residual (alpha is SPD): nothing to update
-  const double rzt = slot_total(red, rz_slot);
-  const double gamma = rzt == 0.0 ? 0.0 : rzt / slot_total(red, S_PQ);
+  double tot[2];
+  slot_totals<2>(red, {rz_slot, S_PQ}, tot);
+  const double gamma = tot[0] == 0.0 ? 0.0 : tot[0] / tot[1];
   if (i < s.npol) {
     const double4 pv = p[i], qv = q[i];
     double4 xv = x[i], rv = r[i];
@@ -70,10 +71,9 @@ __global__ __launch_bounds__(kBlock) void k_update(SysView s, Reduce red, int rz
 // on the same partial sums, so all agree; block 0 raises the flag.  With
 // zz_ref (a device total the host has not read), the replacement threshold
 // is zz_replace * *zz_ref.
-__device__ __forceinline__ bool check_stop(const Reduce& red, int* flag, int iter, double zz_stop,
-                                           double zz_replace, const double* zz_ref) {
-  const double pq = slot_total(red, S_PQ);
-  const double zz = slot_total(red, S_ZZ);
+__device__ __forceinline__ bool check_stop(double pq, double zz, int* flag, int iter,
+                                           double zz_stop, double zz_replace,
+                                           const double* zz_ref) {
   const double zr = zz_ref ? zz_replace * *zz_ref : zz_replace;
   // a converged residual stops first (a zero residual also has p.Tp = 0)
   int reason = 0;
@@ -93,11 +93,12 @@ __global__ __launch_bounds__(kBlock) void k_direction(SysView s, Reduce red, int
                                                       int* flag, int iter, double zz_stop,
                                                       double zz_replace, const double* zz_ref) {
   if (stopped(red.stop)) return;
-  if (flag && check_stop(red, flag, iter, zz_stop, zz_replace, zz_ref)) return;
+  double tot[4];   // p.Tp, z.z and the new and old r.z
+  slot_totals<4>(red, {S_PQ, S_ZZ, num, den}, tot);
+  if (flag && check_stop(tot[0], tot[1], flag, iter, zz_stop, zz_replace, zz_ref)) return;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   // r.z = 0 only for a zero residual (then z = 0 and p = 0 as well)
-  const double rz_old = slot_total(red, den);
-  const double beta = rz_old == 0.0 ? 0.0 : slot_total(red, num) / rz_old;
+  const double beta = tot[3] == 0.0 ? 0.0 : tot[2] / tot[3];
   if (i >= s.npol) return;
   const double4 zv = z[i], pv = p[i];
   const double4 o = make_double4(zv.x + beta * pv.x, zv.y + beta * pv.y, zv.z + beta * pv.z, 0.0);
@@ -165,10 +166,11 @@ __global__ __launch_bounds__(kBlock) void k_check(Reduce red, int* flag, double*
                                                   const double* zz_ref) {
   // z.z of the last update that ran (kernels after a stop leave the
   // partials alone), for the host's batch sizing
-  const double zz = slot_total(red, S_ZZ);
-  if (threadIdx.x == 0) *zz_out = zz;
+  double tot[2];
+  slot_totals<2>(red, {S_PQ, S_ZZ}, tot);
+  if (threadIdx.x == 0) *zz_out = tot[1];
   if (flag[0]) return;
-  (void)check_stop(red, flag, iter, zz_stop, zz_replace, zz_ref);
+  (void)check_stop(tot[0], tot[1], flag, iter, zz_stop, zz_replace, zz_ref);
 }
 
 __global__ void k_copy4(const double4* in, double4* out, float4* out32, int n) {
@@ -305,9 +307,7 @@ void launch_direction(const SysView& s, const Reduce& red, int num, int den, con
 __global__ __launch_bounds__(kBlock) void k_slot_totals(Reduce red, SlotList sl, double* out) {
   const int k = blockIdx.x;
   const int slot = sl.slot[k], n = sl.nparts[k];
-  const double* p = red.partials + (size_t)slot * red.max_blocks;
-  double v = 0.0;
-  for (int b = threadIdx.x; b < n; b += blockDim.x) v += p[b];
+  double v = slot_share(red, slot, n);
   __shared__ double sh[kBlock / 64];
   v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
