@@ -1491,23 +1491,33 @@ int brick_edge(int K, int order, int most) {
   return 0;
 }
 
-// Brick edges of a grid (0 where none fits).  Edges of up to kBrick points
-// unless that leaves bricks for fewer workgroups than the GPU has CUs and
-// the context is FP64: then of kBrickSmall where the grid allows it, since
-// one workgroup adds its brick's sites one after the other (up to 81 sites
-// in a brick of 8^3 points, 24 in one of 4^3).  A mixed context keeps the
-// larger bricks: its FP32 tile sums would round differently.
+// The bricks of a grid's axis: see PmeView.
+struct BrickAxis {
+  int edge = 0, count = 0, bn = 1, bk = 1;   // largest brick, 0 where none fits
+};
+
+// Edges of up to kBrick points unless that leaves bricks for fewer workgroups
+// than the GPU has CUs and the context is FP64: then as many bricks as there
+// are whole runs of kBrickSmall points (order - 1 where that is more), since
+// one workgroup adds its brick's sites one after the other (up to 81 sites in
+// a brick of 8^3 points, 24 in one of 4^3; on a grid of 18^3, bricks of 7, 7
+// and 4 against 5, 4, 5 and 4 points take 16.5 against 7.7 us).  A mixed
+// context keeps the larger bricks: its FP32 tile sums would round differently.
 constexpr int kBrickSmall = 4, kBrickFew = 256;
-void brick_edges(const sibfa_params& p, int edge[3]) {
+void brick_axes(const sibfa_params& p, BrickAxis ax[3]) {
   int bricks = 1;
   for (int a = 0; a < 3; ++a) {
-    edge[a] = brick_edge(p.grid[a], p.order, kBrick);
-    bricks *= edge[a] ? (p.grid[a] + edge[a] - 1) / edge[a] : 1;
+    const int e = brick_edge(p.grid[a], p.order, kBrick);
+    ax[a] = BrickAxis{};
+    if (e) ax[a] = {e, (p.grid[a] + e - 1) / e, 1, e};
+    bricks *= std::max(ax[a].count, 1);
   }
   if (p.precision != SIBFA_FP64 || bricks > kBrickFew) return;
   for (int a = 0; a < 3; ++a) {
-    const int e = brick_edge(p.grid[a], p.order, kBrickSmall);
-    if (e) edge[a] = e;
+    const int K = p.grid[a], nb = K / std::max(kBrickSmall, p.order - 1);
+    if (nb <= ax[a].count) continue;
+    if (K % nb) ax[a] = {(K + nb - 1) / nb, nb, nb, K};
+    else ax[a] = {K / nb, nb, 1, K / nb};
   }
 }
 
@@ -1531,10 +1541,14 @@ sibfa_status setup_pme(sibfa_ctx c) {
   }
   pm.kxh = pm.K[0] / 2 + 1;
   pm.beta = c->prm.ewald_beta;
-  brick_edges(c->prm, pm.Bb);
+  BrickAxis axes[3];
+  brick_axes(c->prm, axes);
   for (int a = 0; a < 3; ++a) {
-    if (pm.Bb[a] == 0) return fail(c, SIBFA_E_ARG, "no spreading brick size fits this grid");
-    pm.nb[a] = (pm.K[a] + pm.Bb[a] - 1) / pm.Bb[a];
+    if (axes[a].edge == 0) return fail(c, SIBFA_E_ARG, "no spreading brick size fits this grid");
+    pm.Bb[a] = axes[a].edge;
+    pm.nb[a] = axes[a].count;
+    pm.bn[a] = axes[a].bn;
+    pm.bk[a] = axes[a].bk;
   }
   c->nbricks = pm.nb[0] * pm.nb[1] * pm.nb[2];
   pm.tile_size = (pm.Bb[0] + order - 1) * (pm.Bb[1] + order - 1) * (pm.Bb[2] + order - 1);
@@ -1733,12 +1747,10 @@ size_t sibfa_footprint_bytes(int n_sites, int n_polarizable, const double* box,
     bytes += (nr * 2 + (size_t)(p->order - 1) * p->grid[1] * p->grid[2]) * (8 + 4) +
              nh * (16 + 8 + 8 + 4);
     size_t tiles = 1;
-    int edge[3];
-    brick_edges(*p, edge);
-    for (int a = 0; a < 3; ++a) {
-      const int e = std::max(edge[a], 1);
-      tiles *= (size_t)((p->grid[a] + e - 1) / e) * (e + p->order - 1);
-    }
+    BrickAxis axes[3];
+    brick_axes(*p, axes);
+    for (int a = 0; a < 3; ++a)
+      tiles *= (size_t)axes[a].count * (axes[a].edge + p->order - 1);
     bytes += tiles * (8 + 4);
     // cell grid as in sibfa_set_system: two counts, two starts; list maxima
     size_t cells = 1;
@@ -1827,12 +1839,9 @@ sibfa_status sibfa_set_system(sibfa_ctx c, int n_sites, const double* xyz, const
   if (c->periodic) {
     mb += (size_t)c->prm.grid[1] * (c->prm.grid[0] / 2 + 1);
     size_t bricks = 1;
-    int edge[3];
-    brick_edges(c->prm, edge);
-    for (int a = 0; a < 3; ++a) {
-      const int e = std::max(edge[a], 1);
-      bricks *= (size_t)((c->prm.grid[a] + e - 1) / e);
-    }
+    BrickAxis axes[3];
+    brick_axes(c->prm, axes);
+    for (int a = 0; a < 3; ++a) bricks *= (size_t)axes[a].count;
     mb = std::max(mb, bricks);
   }
   const int max_blocks = (int)mb;

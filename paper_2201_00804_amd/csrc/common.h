@@ -115,10 +115,12 @@ struct PmeView {
   // (radices 2, 3, 4, 5), so the stage loop decodes them from a scalar
   int nrad[3];
   unsigned radcode[3];
-  // spreading bricks: Bb[0] x Bb[1] x Bb[2] grid points per workgroup (each
-  // <= kBrick; the last brick along an axis may be shorter but never below
-  // order - 1 points), sites binned by the brick holding their base index
-  int Bb[3];
+  // spreading bricks: at most Bb[0] x Bb[1] x Bb[2] grid points per workgroup
+  // (each <= kBrick, none below order - 1 points), sites binned by the brick
+  // holding their base index.  Brick b of an axis starts at ceil(b bk / bn):
+  // bn = 1 and bk = Bb cuts bricks of Bb points and a shorter last one, bn =
+  // nb and bk = K cuts nb bricks of nearly equal length.
+  int Bb[3], bn[3], bk[3];
   int nb[3];
   double* tiles;           // [nbricks][tile_size] spreading tiles
   float* tiles32;
@@ -145,6 +147,13 @@ __device__ __forceinline__ const double* tile_data<double>(const PmeView& pm) { 
 template <>
 __device__ __forceinline__ const float* tile_data<float>(const PmeView& pm) { return pm.tiles32; }
 
+__device__ __forceinline__ int brick_of(const PmeView& pm, int a, int g) {
+  return pm.bn[a] == 1 ? g / pm.bk[a] : g * pm.bn[a] / pm.bk[a];
+}
+__device__ __forceinline__ int brick_start(const PmeView& pm, int a, int b) {
+  return pm.bn[a] == 1 ? b * pm.bk[a] : (b * pm.bk[a] + pm.bn[a] - 1) / pm.bn[a];
+}
+
 template <typename T>
 __device__ __forceinline__ T fold_point(const PmeView& pm, int gx, int gy, int gz) {
   const int P = pm.order;
@@ -152,8 +161,8 @@ __device__ __forceinline__ T fold_point(const PmeView& pm, int gx, int gy, int g
   int bi[3][2], ti[3][2], nd[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const int B = pm.Bb[a], b = g[a] / B, ox = g[a] - b * B;
-    const int Bs = min(B, pm.K[a] - b * B);
+    const int b = brick_of(pm, a, g[a]), o = brick_start(pm, a, b), ox = g[a] - o;
+    const int Bs = min(brick_start(pm, a, b + 1), pm.K[a]) - o;
     bi[a][0] = b;
     ti[a][0] = ox + P - 1;
     bi[a][1] = b + 1 < pm.nb[a] ? b + 1 : 0;

@@ -17,8 +17,7 @@ namespace sibfa {
 
 // ------------------------------------------------------------ spreading
 // Sites are binned by home brick, the brick of B^3 grid points (B <= 8, per
-// axis; the last brick along an axis never has fewer than p - 1 points)
-// holding their base index b.  A site touches points b - t, t = 0..p-1, so
+// axis; no brick has fewer than p - 1 points along an axis) holding their base index b.  A site touches points b - t, t = 0..p-1, so
 // all contributions of a brick's sites fall in the brick extended by p - 1
 // points towards lower indices: its tile, (B + p - 1)^3 points.
 //
@@ -29,7 +28,7 @@ namespace sibfa {
 //                  points of the next brick, that brick's -- in a fixed
 //                  order.  No global atomics, no clearing, deterministic.
 //                  k_spread_fold writes the real grid Q the convolution
-//                  starts from.
+//                  starts from, or its first pass sums the tiles itself.
 
 // Sites come in cell-sorted order, so a wavefront's sites fall in a few
 // bricks: one counter atomic per run of equal bricks.  One pass bins all
@@ -47,7 +46,7 @@ __global__ void k_brick_bin(SysView s, PmeView pm, int3* slot, int* count_all, i
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       double fr;
-      h[a] = grid_base(x[a], pm.scale[a], pm.K[a], &fr) / pm.Bb[a];
+      h[a] = brick_of(pm, a, grid_base(x[a], pm.scale[a], pm.K[a], &fr));
     }
     b = h[0] + pm.nb[0] * (h[1] + pm.nb[1] * h[2]);
   }
@@ -241,8 +240,8 @@ __global__ __launch_bounds__(128) void k_spread_tile(SysView s, PmeView pm, cons
   // highest one and places of their weights (a lane past the support repeats
   // the last point: the same value written twice)
   const int sj = lane / 3, ax = lane - 3 * sj;
-  const int o = ax == 0 ? (b % nb0) * pm.Bb[0]
-                        : ax == 1 ? ((b / nb0) % nb1) * pm.Bb[1] : (b / (nb0 * nb1)) * pm.Bb[2];
+  const int o = brick_start(pm, ax, ax == 0 ? b % nb0 : ax == 1 ? (b / nb0) % nb1
+                                                                : b / (nb0 * nb1));
   int dx[NR], dy[NR], dz[NR], off[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
