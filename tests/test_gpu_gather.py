@@ -37,3 +37,25 @@ def test_rows_over_the_edge(monkeypatch, planes, order, grid, precision):
         eng.solve()
         assert rel_err(eng.energy_forces()[2].cpu().numpy(), oracle.evaluate(s, prm)["forces"]) < 1e-7
     eng.close()
+
+
+@pytest.mark.parametrize("grid", [(64, 64, 16), (64, 72, 16), (16, 10, 18)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_fold_in_the_plane_pass(monkeypatch, grid, precision):
+    """Planes up to and past the largest that sum the spreading tiles in the
+    first pass of the convolution, against the five-pass convolution, which
+    never does (the same sums and another order of the transforms: rounding,
+    1e-12 of FP64 and 1e-5 of FP32)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    say(f"[gather] fold grid {grid} {precision}")
+    d = water_box_ortho((3, 4, 4), (3.105,) * 3, 13)
+    p = torch.as_tensor(np.random.default_rng(4).standard_normal((len(d["pos"]), 3)), device="cuda")
+    out = []
+    for planes in ("1", "0"):
+        monkeypatch.setenv("SIBFA_FFT_PLANES", planes)
+        eng = engine_for(d, gpu_params(d, precision=precision, beta=0.5, cutoff=4.5, grid=grid))
+        out.append((eng.permanent_field().cpu().numpy(), eng.apply_T(p).cpu().numpy()))
+        eng.close()
+    tol = 1e-12 if precision == "fp64" else 1e-5
+    assert rel_err(out[0][0], out[1][0]) < tol and rel_err(out[0][1], out[1][1]) < tol
