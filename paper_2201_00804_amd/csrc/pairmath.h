@@ -136,7 +136,7 @@ __device__ __forceinline__ void thole_tp(R x, R tp[5]) {
 }
 
 // The same in FP64 for the kernels that evaluate every pair of a list
-// (about 300 FP64 instructions each, which is what bounds them): 2^k times a
+// (200 to 300 FP64 instructions each, which is what bounds them): 2^k times a
 // polynomial of degree 11 for exp(-x^2), without the library's special cases
 // (the argument is finite and never positive; below -700 it is taken there,
 // 1e-304), and the erfcx series by Horner's rule, half Clenshaw's steps.
@@ -291,7 +291,7 @@ __device__ __forceinline__ void mp_field(const R c[6], const MP<R>& B, const R R
 // out, as in mp_pair (they meet its trace, which is zero).  The FP64 pair loops
 // are bound by their instructions: sums instead of pair energies and forces,
 // with the functions above, take 388 vector instructions per entry of the
-// force to 245 and 254 of the permanent field to 190; over 160,000 sites
+// force to 270 and 254 of the permanent field to 211; over 160,000 sites
 // (cutoff 9, 509 entries each) 1270 us became 810 and 950 became 610.
 struct PotSums {
   double e[3];         // d_a phi

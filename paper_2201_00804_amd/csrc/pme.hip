@@ -146,7 +146,8 @@ __device__ __forceinline__ void spread_weights(R w, R th[ND + 1][P]) {
 // site; splitting the tile's planes over four waves leaves each of them
 // most of the sites.  Dipole spread, thread per column -> this: 28 -> 16 us
 // at 4,096 waters (FP32), 81 -> 40 us at 32,000 (FP64, beside the matvec);
-// all multipoles 53 -> 32 us at 216 waters.
+// all multipoles 53 -> 32 us in the 27 bricks of 18^3 points that 216 waters
+// had (13 us in the 64 they have now).
 // The brick lists are sorted by site index when they are built and one wave
 // adds them in that order, so the tile sums -- and the grid -- are
 // reproducible bit for bit.
