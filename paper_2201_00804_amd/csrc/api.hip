@@ -1079,6 +1079,10 @@ sibfa_status solve(sibfa_ctx c, bool warm) {
     c->red.stop = flag;
     c->pm.stop = flag;
     int j = 0, j_done = 0, reason = 0;   // iterations of this run
+    // few sites, diagonal preconditioner: an iteration ends with the next one's
+    // direction (launch_step)
+    const bool step = !blk && c->npol <= kStepSites;
+    bool p_ready = false;
     for (;;) {
       if (c->prof && c->marks.size() > 4096) fold_marks(c);
       int nb = 4;
@@ -1095,8 +1099,9 @@ sibfa_status solve(sibfa_ctx c, bool warm) {
         c->cur_tag = j;
         // with two streams, the direction kernel's own completion records
         // the fork event (a separate marker cost the main stream ~5 us)
-        const bool fork_by_dir = k > 0 && c->periodic && c->aux != c->stream;
-        if (k > 0) {
+        const bool two = c->periodic && c->aux != c->stream;
+        const bool fork_by_dir = two && (k > 0 || p_ready);
+        if (k > 0 && !p_ready) {
           // p = z + beta p, after the stop test of the previous iteration
           // when that was enqueued in this batch
           const int num = S_RZ0 + (k & 1), den = S_RZ0 + ((k - 1) & 1);
@@ -1137,15 +1142,19 @@ sibfa_status solve(sibfa_ctx c, bool warm) {
         }
         {
           Phase ph(c, SIBFA_PH_UPDATE);
-          if (blk)
-            launch_pc_update(s, c->pcv, c->red, S_RZ0 + (k & 1), S_RZ0 + ((k + 1) & 1), c->x,
-                             c->r, c->z, c->p, c->q, st);
+          const int rz = S_RZ0 + (k & 1), rz_next = S_RZ0 + ((k + 1) & 1);
+          if (step)
+            launch_step(s, c->red, rz, rz_next, c->x, c->r, c->z, c->p,
+                        c->p32, c->q, flag, zz_dev, j + 1, zz_stop, zz_replace, zz_ref, st,
+                        two ? c->ev_fork : nullptr);
+          else if (blk)
+            launch_pc_update(s, c->pcv, c->red, rz, rz_next, c->x, c->r, c->z, c->p, c->q, st);
           else
-            launch_update(s, c->red, S_RZ0 + (k & 1), S_RZ0 + ((k + 1) & 1), c->x, c->r, c->z,
-                          c->p, c->q, st);
+            launch_update(s, c->red, rz, rz_next, c->x, c->r, c->z, c->p, c->q, st);
+          p_ready = step;
           // the last iteration of a batch is tested here, the others by
           // the next direction update
-          if (b == nb - 1 || it + j + 1 >= c->prm.max_iter)
+          if (!step && (b == nb - 1 || it + j + 1 >= c->prm.max_iter))
             launch_check(c->red, flag, zz_dev, j + 1, zz_stop, zz_replace, zz_ref, st);
         }
         ++j;

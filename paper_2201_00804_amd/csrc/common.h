@@ -15,6 +15,7 @@ constexpr double kSqrtPi = 1.7724538509055160273;
 constexpr double kPi = 3.14159265358979323846;
 
 constexpr int kBlock = 256;      // threads per block for site-parallel kernels
+constexpr int kBlockMax = 512;   // largest workgroup that reads slot totals
 constexpr int kMaxOrder = 6;     // largest B-spline order supported
 
 // Reduction slots (each has partials, a completion counter and a scalar).
@@ -353,7 +354,7 @@ __device__ __forceinline__ double slot_share(const Reduce& red, int slot, int n)
 template <int N>
 __device__ __forceinline__ void slot_totals(const Reduce& red, const int (&slot)[N],
                                             double (&out)[N]) {
-  __shared__ double sh[N][kBlock / 64];
+  __shared__ double sh[N][kBlockMax / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   double v[N];
 #pragma unroll

@@ -87,6 +87,13 @@ void launch_direction(const SysView& s, const Reduce& red, int num, int den, con
                       double4* p, float4* p32, int* flag, int iter, double zz_stop,
                       double zz_replace, const double* zz_ref, hipStream_t st,
                       hipEvent_t done = nullptr);
+// launch_update, launch_check and launch_direction in one launch of one
+// workgroup, for up to kStepSites polarizable sites, to the same bits
+constexpr int kStepSites = 1024;
+void launch_step(const SysView& s, Reduce& red, int rz_slot, int rz_next_slot, double4* x,
+                 double4* r, double4* z, double4* p, float4* p32, const double4* q, int* flag,
+                 double* zz_out, int iter, double zz_stop, double zz_replace,
+                 const double* zz_ref, hipStream_t st, hipEvent_t done);
 void launch_nonfinite(const double* v, size_t n, int* flag, hipStream_t st);
 // Totals of up to 8 reduction slots (one block each, fixed order) into out.
 struct SlotList {

@@ -18,6 +18,49 @@ __device__ __forceinline__ double3 amul(const double* a, double4 v) {
                       a[2] * v.x + a[4] * v.y + a[5] * v.z);
 }
 
+// Stop test of the previous iteration (see k_check), made by every block
+// on the same partial sums, so all agree; block 0 raises the flag.  With
+// zz_ref (a device total the host has not read), the replacement threshold
+// is zz_replace * *zz_ref.
+__device__ __forceinline__ bool check_stop(double pq, double zz, int* flag, int iter,
+                                           double zz_stop, double zz_replace,
+                                           const double* zz_ref) {
+  const double zr = zz_ref ? zz_replace * *zz_ref : zz_replace;
+  // a converged residual stops first (a zero residual also has p.Tp = 0)
+  int reason = 0;
+  if (zz <= zz_stop) reason = 1;
+  else if (!(pq > 0.0)) reason = 2;
+  else if (zz <= zr) reason = 3;
+  if (reason && blockIdx.x == 0 && threadIdx.x == 0) {
+    flag[1] = reason; flag[2] = iter; flag[0] = 1;
+  }
+  return reason != 0;
+}
+
+// x += gamma p, r -= gamma q, z = alpha r of site i; r.z and z.z.
+__device__ __forceinline__ void update_site(const SysView& s, int i, double gamma, double4* x,
+                                            double4* r, double4* z, const double4* p,
+                                            const double4* q, double& rz, double& zz) {
+  const double4 pv = p[i], qv = q[i];
+  double4 xv = x[i], rv = r[i];
+  xv.x += gamma * pv.x; xv.y += gamma * pv.y; xv.z += gamma * pv.z;
+  rv.x -= gamma * qv.x; rv.y -= gamma * qv.y; rv.z -= gamma * qv.z;
+  const double3 zv = amul(s.alpha + 6 * (size_t)i, rv);
+  x[i] = xv;
+  r[i] = rv;
+  z[i] = make_double4(zv.x, zv.y, zv.z, 0.0);
+  rz = rv.x * zv.x + rv.y * zv.y + rv.z * zv.z;
+  zz = zv.x * zv.x + zv.y * zv.y + zv.z * zv.z;
+}
+// p = z + beta p
+__device__ __forceinline__ void direction_site(int i, double beta, const double4* z, double4* p,
+                                               float4* p32) {
+  const double4 zv = z[i], pv = p[i];
+  const double4 o = make_double4(zv.x + beta * pv.x, zv.y + beta * pv.y, zv.z + beta * pv.z, 0.0);
+  p[i] = o;
+  p32[i] = make_float4((float)o.x, (float)o.y, (float)o.z, 0.f);
+}
+
 __global__ __launch_bounds__(kBlock) void k_init_residual(SysView s, Reduce red, const double4* E0,
                                                           const double4* t, double4* r, double4* z,
                                                           double4* p, float4* p32, int rz_slot) {
@@ -51,39 +94,9 @@ __global__ __launch_bounds__(kBlock) void k_update(SysView s, Reduce red, int rz
   double tot[2];
   slot_totals<2>(red, {rz_slot, S_PQ}, tot);
   const double gamma = tot[0] == 0.0 ? 0.0 : tot[0] / tot[1];
-  if (i < s.npol) {
-    const double4 pv = p[i], qv = q[i];
-    double4 xv = x[i], rv = r[i];
-    xv.x += gamma * pv.x; xv.y += gamma * pv.y; xv.z += gamma * pv.z;
-    rv.x -= gamma * qv.x; rv.y -= gamma * qv.y; rv.z -= gamma * qv.z;
-    const double3 zv = amul(s.alpha + 6 * (size_t)i, rv);
-    x[i] = xv;
-    r[i] = rv;
-    z[i] = make_double4(zv.x, zv.y, zv.z, 0.0);
-    rz = rv.x * zv.x + rv.y * zv.y + rv.z * zv.z;
-    zz = zv.x * zv.x + zv.y * zv.y + zv.z * zv.z;
-  }
+  if (i < s.npol) update_site(s, i, gamma, x, r, z, p, q, rz, zz);
   block_partial(rz, red, rz_next_slot);
   block_partial(zz, red, S_ZZ);
-}
-
-// Stop test of the previous iteration (see k_check), made by every block
-// on the same partial sums, so all agree; block 0 raises the flag.  With
-// zz_ref (a device total the host has not read), the replacement threshold
-// is zz_replace * *zz_ref.
-__device__ __forceinline__ bool check_stop(double pq, double zz, int* flag, int iter,
-                                           double zz_stop, double zz_replace,
-                                           const double* zz_ref) {
-  const double zr = zz_ref ? zz_replace * *zz_ref : zz_replace;
-  // a converged residual stops first (a zero residual also has p.Tp = 0)
-  int reason = 0;
-  if (zz <= zz_stop) reason = 1;
-  else if (!(pq > 0.0)) reason = 2;
-  else if (zz <= zr) reason = 3;
-  if (reason && blockIdx.x == 0 && threadIdx.x == 0) {
-    flag[1] = reason; flag[2] = iter; flag[0] = 1;
-  }
-  return reason != 0;
 }
 
 // p = z + beta p with beta = scalars[num] / scalars[den] (no grid to spread),
@@ -100,10 +113,7 @@ __global__ __launch_bounds__(kBlock) void k_direction(SysView s, Reduce red, int
   // r.z = 0 only for a zero residual (then z = 0 and p = 0 as well)
   const double beta = tot[3] == 0.0 ? 0.0 : tot[2] / tot[3];
   if (i >= s.npol) return;
-  const double4 zv = z[i], pv = p[i];
-  const double4 o = make_double4(zv.x + beta * pv.x, zv.y + beta * pv.y, zv.z + beta * pv.z, 0.0);
-  p[i] = o;
-  p32[i] = make_float4((float)o.x, (float)o.y, (float)o.z, 0.f);
+  direction_site(i, beta, z, p, p32);
 }
 
 // x += w z (the peek step of the truncated solver)
@@ -303,6 +313,74 @@ void launch_direction(const SysView& s, const Reduce& red, int num, int den, con
     hipLaunchKernelGGL(k_direction, grid_for(s.npol), dim3(kBlock), 0, st, s, red, num, den, z, p,
                        p32, flag, iter, zz_stop, zz_replace, zz_ref);
 }
+// The whole step between two products for few sites.  Update and direction are
+// bound by their launches and by each one's chain of totals, vectors and sums;
+// here one workgroup keeps the totals to itself (solves with it: 20 waters 428
+// -> 381 us, 80 487 -> 433, 300 764 -> 735, a box of 216 1282 -> 1206).  Past
+// kStepSites one CU takes longer over the vectors than the launch it saves.
+// The block preconditioner stays with its own kernels: in one workgroup its
+// factors take as long (216 waters: 13.5 us against 7.5 + 5.2).  Every sum is
+// made in the order of the kernels this one stands for: a wavefront, the four
+// wavefronts of kBlock sites, those partials (also left in their slots, for the
+// next totals).
+constexpr int kStepThreads = 512;
+__global__ __launch_bounds__(kStepThreads) void k_step(
+    SysView s, Reduce red, int rz_slot, int rz_next_slot, double4* x, double4* r,
+    double4* z, double4* p, float4* p32, const double4* q, int* flag, double* zz_out, int iter,
+    double zz_stop, double zz_replace, const double* zz_ref) {
+  if (stopped(red.stop)) return;
+  constexpr int W = kStepThreads / 64, PW = kBlock / 64;
+  __shared__ double sh[2][kStepSites / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  double tot[2];
+  slot_totals<2>(red, {rz_slot, S_PQ}, tot);
+  // r.z = 0 only for a zero residual: nothing to update
+  const double gamma = tot[0] == 0.0 ? 0.0 : tot[0] / tot[1];
+  for (int c = 0; c < kStepSites / kStepThreads; ++c) {
+    const int i = c * kStepThreads + tid;
+    double rz = 0.0, zz = 0.0;
+    if (i < s.npol) update_site(s, i, gamma, x, r, z, p, q, rz, zz);
+    rz = wave_sum(rz);
+    zz = wave_sum(zz);
+    if (lane == 0) {
+      sh[0][c * W + wid] = rz;
+      sh[1][c * W + wid] = zz;
+    }
+  }
+  __syncthreads();
+  // every wavefront adds up the partials, one per lane
+  const int nb = (s.npol + kBlock - 1) / kBlock;
+  double part[2] = {0.0, 0.0};
+  if (lane < nb)
+    for (int w = 0; w < PW; ++w) {
+      part[0] += sh[0][lane * PW + w];
+      part[1] += sh[1][lane * PW + w];
+    }
+  if (tid < nb) {
+    red.partials[(size_t)rz_next_slot * red.max_blocks + tid] = part[0];
+    red.partials[(size_t)S_ZZ * red.max_blocks + tid] = part[1];
+  }
+  const double rz_new = wave_sum(part[0]), zz = wave_sum(part[1]);
+  if (tid == 0) *zz_out = zz;
+  if (check_stop(tot[1], zz, flag, iter, zz_stop, zz_replace, zz_ref)) return;
+  const double beta = tot[0] == 0.0 ? 0.0 : rz_new / tot[0];
+  for (int i = tid; i < s.npol; i += kStepThreads) direction_site(i, beta, z, p, p32);
+}
+
+void launch_step(const SysView& s, Reduce& red, int rz_slot, int rz_next_slot, double4* x,
+                 double4* r, double4* z, double4* p, float4* p32, const double4* q, int* flag,
+                 double* zz_out, int iter, double zz_stop, double zz_replace,
+                 const double* zz_ref, hipStream_t st, hipEvent_t done) {
+  if (done)   // the kernel's own completion records the event: no marker packet
+    hipExtLaunchKernelGGL(k_step, dim3(1), dim3(kStepThreads), 0, st, nullptr, done, 0, s, red,
+                          rz_slot, rz_next_slot, x, r, z, p, p32, q, flag, zz_out, iter, zz_stop,
+                          zz_replace, zz_ref);
+  else
+    hipLaunchKernelGGL(k_step, dim3(1), dim3(kStepThreads), 0, st, s, red, rz_slot, rz_next_slot,
+                       x, r, z, p, p32, q, flag, zz_out, iter, zz_stop, zz_replace, zz_ref);
+  red.nparts[rz_next_slot] = red.nparts[S_ZZ] = (int)grid_for(s.npol).x;
+}
+
 // One block per slot: the slot's partials summed in a fixed order.
 __global__ __launch_bounds__(kBlock) void k_slot_totals(Reduce red, SlotList sl, double* out) {
   const int k = blockIdx.x;
