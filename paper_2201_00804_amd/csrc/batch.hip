@@ -392,38 +392,34 @@ __device__ __forceinline__ R thole_y(const Site<R>& A, const Site<R>& B, R r2, R
 }
 
 // ---------------------------------------------------------------- field
-// Permanent field at site i (zero unless polarizable) and half the MM energy
-// of its pairs, summed over its sixteen lanes.
+// Site j's part of the permanent field at site i (none unless that is
+// polarizable) and half the MM energy of the pair.
 template <typename R>
-__device__ __forceinline__ void field_site(const double4* rec, int n, int i, int lane, double E[3],
+__device__ __forceinline__ void field_pair(const Site<R>& A, const Site<R>& B, double E[3],
                                            double& U) {
-  Site<R> A;
-  load_rec<R>(rec, i, A);
-  E[0] = E[1] = E[2] = 0.0;
-  U = 0.0;
-  for (int j = lane; j < n; j += kClG) {
-    Site<R> B;
-    load_rec<R>(rec, j, B);
-    if (B.mol == A.mol) continue;
-    R Rv[3], r2, r, c0[5];
-    bare_pair<R, 4>(A.x, B.x, Rv, r2, r, c0);
-    U += 0.5 * (double)pair_energy<R>(c0, A.M, B.M, Rv);
-    if (A.s > 0.0) {
-      R cc[5] = {c0[0], c0[1], c0[2], c0[3], R(0)};
-      if (B.s > 0.0) {
-        const R y = thole_y<R>(A, B, r2, r), sij = R(A.s * B.s);
-        R tp[5];
-        thole_pair4<R>(y * sij, ma(y, sij, R(1)), false, tp);
+#pragma clang fp contract(off)
+  if (B.mol == A.mol) return;
+  R Rv[3], r2, r, c0[5];
+  bare_pair<R, 4>(A.x, B.x, Rv, r2, r, c0);
+  U += 0.5 * (double)pair_energy<R>(c0, A.M, B.M, Rv);
+  if (A.s > 0.0) {
+    R cc[5] = {c0[0], c0[1], c0[2], c0[3], R(0)};
+    if (B.s > 0.0) {
+      const R y = thole_y<R>(A, B, r2, r), sij = R(A.s * B.s);
+      R tp[5];
+      thole_pair4<R>(y * sij, ma(y, sij, R(1)), false, tp);
 #pragma unroll
-        for (int k = 1; k <= 3; ++k) cc[k] = ma(-tp[k], c0[k], c0[k]);
-      }
-      R F[3];
-      pair_field<R>(cc, B.M, Rv, F);
-      E[0] += (double)F[0];
-      E[1] += (double)F[1];
-      E[2] += (double)F[2];
+      for (int k = 1; k <= 3; ++k) cc[k] = ma(-tp[k], c0[k], c0[k]);
     }
+    R F[3];
+    pair_field<R>(cc, B.M, Rv, F);
+    E[0] += (double)F[0];
+    E[1] += (double)F[1];
+    E[2] += (double)F[2];
   }
+}
+// Both summed over a site's sixteen lanes.
+__device__ __forceinline__ void field_sum(double E[3], double& U) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) E[k] = group_sum<kClG>(E[k]);
   U = group_sum<kClG>(U);
@@ -671,71 +667,54 @@ __device__ __forceinline__ void same_molecule_force(R c2, R c3, const R a[3], co
     F[k] = ma(Rv[k], rad, -(c2 * ma(-da, b[k], -(a[k] * db))));
 }
 
-// Force on site i (e^2/A^2) at the dipoles mu(j), summed over its sixteen
-// lanes.
-template <typename R, typename MU>
-__device__ __forceinline__ void force_site(const double4* rec, MU mu, int n, int i, int lane,
-                                           double F[3]) {
+// Force (e^2/A^2) on site A with dipole mui of another site B with dipole
+// muj; P is A's multipoles with mui added.
+template <typename R>
+__device__ __forceinline__ void site_force(const Site<R>& A, const MP<R>& P, const R mui[3],
+                                           const Site<R>& B, const R muj[3], double F[3]) {
 #pragma clang fp contract(off)
-  Site<R> A;
-  load_rec<R>(rec, i, A);
-  R mui[3];
-  mu(i, mui);
-  MP<R> Pi = A.M;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) Pi.d[k] += mui[k];
-  F[0] = F[1] = F[2] = 0.0;
-  for (int j = lane; j < n; j += kClG) {
-    if (j == i) continue;
-    Site<R> B;
-    load_rec<R>(rec, j, B);
-    R muj[3];
-    mu(j, muj);
-    R Rv[3], r2, r, c0[6];
-    bare_pair<R, 5>(A.x, B.x, Rv, r2, r, c0);
-    const bool both = A.s > 0.0 && B.s > 0.0;
-    const R x = both ? thole_y<R>(A, B, r2, r) * R(A.s * B.s) : R(0);
-    R f[3];
-    if (B.mol == A.mol) {
-      // same molecule: damped mu-mu only
-      if (!both) continue;
-      R l[5];
-      thole_pair4<R>(x, R(1) + x, true, l);
-      same_molecule_force<R>(l[2] * c0[2], l[3] * c0[3], mui, muj, Rv, f);
-      F[0] += (double)f[0];
-      F[1] += (double)f[1];
-      F[2] += (double)f[2];
-      continue;
-    }
-    R cc[6], D[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
-#pragma unroll
-    for (int k = 0; k < 6; ++k) cc[k] = c0[k];
-    const bool damp = both && x < R(50);
-    if (damp) {
-      R tp[5];
-      thole_pair4<R>(x, R(1) + x, false, tp);
-#pragma unroll
-      for (int k = 1; k <= 4; ++k) {
-        D[k] = tp[k] * c0[k];
-        cc[k] = ma(-tp[k], c0[k], c0[k]);
-      }
-    }
-    MP<R> Pj = B.M;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) Pj.d[k] += muj[k];
-    pair_force<R, false>(cc, Pi, Pj, Rv, f);
+  R Rv[3], r2, r, c0[6];
+  bare_pair<R, 5>(A.x, B.x, Rv, r2, r, c0);
+  const bool both = A.s > 0.0 && B.s > 0.0;
+  const R x = both ? thole_y<R>(A, B, r2, r) * R(A.s * B.s) : R(0);
+  R f[3];
+  if (B.mol == A.mol) {
+    // same molecule: damped mu-mu only
+    if (!both) return;
+    R l[5];
+    thole_pair4<R>(x, R(1) + x, true, l);
+    same_molecule_force<R>(l[2] * c0[2], l[3] * c0[3], mui, muj, Rv, f);
     F[0] += (double)f[0];
     F[1] += (double)f[1];
     F[2] += (double)f[2];
-    if (damp) {
-      pair_force<R, true>(D, A.M, B.M, Rv, f);
-      F[0] += (double)f[0];
-      F[1] += (double)f[1];
-      F[2] += (double)f[2];
+    return;
+  }
+  R cc[6], D[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
+#pragma unroll
+  for (int k = 0; k < 6; ++k) cc[k] = c0[k];
+  const bool damp = both && x < R(50);
+  if (damp) {
+    R tp[5];
+    thole_pair4<R>(x, R(1) + x, false, tp);
+#pragma unroll
+    for (int k = 1; k <= 4; ++k) {
+      D[k] = tp[k] * c0[k];
+      cc[k] = ma(-tp[k], c0[k], c0[k]);
     }
   }
+  MP<R> Pj = B.M;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) F[k] = group_sum<kClG>(F[k]);
+  for (int k = 0; k < 3; ++k) Pj.d[k] += muj[k];
+  pair_force<R, false>(cc, P, Pj, Rv, f);
+  F[0] += (double)f[0];
+  F[1] += (double)f[1];
+  F[2] += (double)f[2];
+  if (damp) {
+    pair_force<R, true>(D, A.M, B.M, Rv, f);
+    F[0] += (double)f[0];
+    F[1] += (double)f[1];
+    F[2] += (double)f[2];
+  }
 }
 
 __device__ __forceinline__ double quiet_nan() { return __longlong_as_double(0x7ff8000000000000ll); }
@@ -797,8 +776,15 @@ __device__ __forceinline__ void small_clusters(const ClusterArgs& a, SmallLds<R>
     __syncthreads();
     double U = 0.0;
     for (int i = slot; i < n; i += nslot) {
-      double E[3], u;
-      field_site<R>(rec, n, i, lane, E, u);
+      Site<R> A;
+      load_rec<R>(rec, i, A);
+      double E[3] = {0.0, 0.0, 0.0}, u = 0.0;
+      for (int j = lane; j < n; j += kClG) {
+        Site<R> B;
+        load_rec<R>(rec, j, B);
+        field_pair<R>(A, B, E, u);
+      }
+      field_sum(E, u);
       if (lane == 0) {
         U += u;
         lE[i] = make_double4(E[0], E[1], E[2], 0.0);
@@ -887,8 +873,21 @@ __device__ __forceinline__ void small_clusters(const ClusterArgs& a, SmallLds<R>
       m[0] = (R)v.x; m[1] = (R)v.y; m[2] = (R)v.z;
     };
     for (int i = slot; i < n; i += nslot) {
-      double F[3];
-      force_site<R>(rec, mu, n, i, lane, F);
+      Site<R> A;
+      load_rec<R>(rec, i, A);
+      R mui[3], muj[3];
+      mu(i, mui);
+      MP<R> P = A.M;
+      for (int k = 0; k < 3; ++k) P.d[k] += mui[k];
+      double F[3] = {0.0, 0.0, 0.0};
+      for (int j = lane; j < n; j += kClG) {
+        if (j == i) continue;
+        Site<R> B;
+        load_rec<R>(rec, j, B);
+        mu(j, muj);
+        site_force<R>(A, P, mui, B, muj, F);
+      }
+      for (int k = 0; k < 3; ++k) F[k] = group_sum<kClG>(F[k]);
       if (lane == 0)
         for (int k = 0; k < 3; ++k) a.forces[3 * (size_t)(base + i) + k] = kCoulomb * F[k];
     }
@@ -923,21 +922,88 @@ __global__ __launch_bounds__(kClBlock) void k_cl_prep(ClusterArgs a, int count) 
   }
 }
 
+// A chunk of a cluster's sites in LDS, in the pairs' precision, for the field
+// and force sums of sixteen sites.  With every lane reading and converting its
+// neighbour's record from memory (four 32-byte loads a pair, sixteen sites'
+// records per wavefront) many clusters took longer than the pairs' arithmetic:
+// 1,000 clusters of 64 waters, field and forces 1,586 + 1,588 -> 407 + 590 us
+// (mixed), 1,622 + 1,575 -> 648 + 1,090 (FP64); 1,000 of 13 to 20 waters (mixed)
+// 144 + 133 -> 66 + 71 us; 48 of 64 waters as a whole 417 -> 305 us.
+// An odd number of 16-byte words per site: the sixteen lanes' reads fall in
+// different banks.
+constexpr int kClStage = 128;
+template <typename R>
+struct alignas(16) StagedSite {
+  double x[3], s;
+  MP<R> M;
+  double th;
+  R mu[3];
+  int mol, pad[4];
+};
+static_assert(sizeof(StagedSite<float>) / 16 % 2 == 1 && sizeof(StagedSite<double>) / 16 % 2 == 1,
+              "bank spread of the staged sites");
+
+// Sites [j0, j0 + count) of a cluster, with their dipoles where gmu is given.
+template <typename R>
+__device__ __forceinline__ void stage_sites(const double4* rec, const double* gmu, int j0,
+                                            int count, StagedSite<R>* l) {
+  const int t = threadIdx.x;
+  __syncthreads();   // the chunk before is read
+  if (t < count) {
+    Site<R> S;
+    load_rec<R>(rec, j0 + t, S);
+    StagedSite<R>& o = l[t];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      o.x[k] = S.x[k];
+      o.mu[k] = gmu ? (R)gmu[3 * (j0 + t) + k] : R(0);
+    }
+    o.s = S.s;
+    o.M = S.M;
+    o.th = S.th;
+    o.mol = S.mol;
+  }
+  __syncthreads();
+}
+template <typename R>
+__device__ __forceinline__ void staged_site(const StagedSite<R>& o, Site<R>& S) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) S.x[k] = o.x[k];
+  S.M = o.M;
+  S.s = o.s;
+  S.th = o.th;
+  S.mol = o.mol;
+}
+
 // gridDim.y workgroups per cluster walk its sites, sixteen at a time
 // (blockIdx.z = 0: field and MM energy), or its rows of the coefficient
 // table (blockIdx.z = 1).
 template <typename R>
 __global__ __launch_bounds__(kClBlock) void k_cl_field(ClusterArgs a, int count) {
+  __shared__ StagedSite<R> l[kClStage];
   const int t = threadIdx.x, slot = t / kClG, lane = t % kClG;
   for (int b = blockIdx.x; b < count; b += gridDim.x) {
     int c, base, n;
     if (!large_cluster(a, b, c, base, n)) continue;
     const double4* rec = a.rec + 4 * (size_t)base;
     if (blockIdx.z == 0) {
-      for (int i = blockIdx.y * kClTile + slot; i < n; i += gridDim.y * kClTile) {
-        double E[3], u;
-        field_site<R>(rec, n, i, lane, E, u);
-        if (lane == 0) {
+      for (int i0 = blockIdx.y * kClTile; i0 < n; i0 += gridDim.y * kClTile) {
+        const int i = i0 + slot;
+        Site<R> A;
+        load_rec<R>(rec, min(i, n - 1), A);
+        double E[3] = {0.0, 0.0, 0.0}, u = 0.0;
+        for (int j0 = 0; j0 < n; j0 += kClStage) {
+          const int m = min(kClStage, n - j0);
+          stage_sites<R>(rec, nullptr, j0, m, l);
+          if (i >= n) continue;
+          for (int j = lane; j < m; j += kClG) {
+            Site<R> B;
+            staged_site<R>(l[j], B);
+            field_pair<R>(A, B, E, u);
+          }
+        }
+        field_sum(E, u);
+        if (lane == 0 && i < n) {
           a.usite[base + i] = u;
           const int k = a.prank[base + i];
           if (k >= 0) a.E0[base + k] = make_double4(E[0], E[1], E[2], 0.0);
@@ -1081,19 +1147,37 @@ __global__ __launch_bounds__(kClSolveBlock) void k_cl_solve(ClusterArgs a, int c
 
 template <typename R>
 __global__ __launch_bounds__(kClBlock) void k_cl_force(ClusterArgs a, int count) {
+  __shared__ StagedSite<R> l[kClStage];
   const int t = threadIdx.x, slot = t / kClG, lane = t % kClG;
   for (int b = blockIdx.x; b < count; b += gridDim.x) {
     int c, base, n;
     if (!large_cluster(a, b, c, base, n)) continue;
     const bool zero = a.status[c] == (int)SIBFA_E_ARG;
     const double* gmu = a.mu + 3 * (size_t)base;
-    auto mu = [&](int j, R m[3]) {
-      m[0] = (R)gmu[3 * j]; m[1] = (R)gmu[3 * j + 1]; m[2] = (R)gmu[3 * j + 2];
-    };
-    for (int i = blockIdx.y * kClTile + slot; i < n; i += gridDim.y * kClTile) {
+    const double4* rec = a.rec + 4 * (size_t)base;
+    for (int i0 = blockIdx.y * kClTile; i0 < n; i0 += gridDim.y * kClTile) {
+      const int i = i0 + slot, is = min(i, n - 1);
       double F[3] = {0.0, 0.0, 0.0};
-      if (!zero) force_site<R>(a.rec + 4 * (size_t)base, mu, n, i, lane, F);
-      if (lane == 0)
+      Site<R> A;
+      load_rec<R>(rec, is, A);
+      const R mui[3] = {(R)gmu[3 * is], (R)gmu[3 * is + 1], (R)gmu[3 * is + 2]};
+      MP<R> P = A.M;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) P.d[k] += mui[k];
+      for (int j0 = 0; j0 < (zero ? 0 : n); j0 += kClStage) {
+        const int m = min(kClStage, n - j0);
+        stage_sites<R>(rec, gmu, j0, m, l);
+        if (i >= n) continue;
+        for (int j = lane; j < m; j += kClG) {
+          if (j0 + j == i) continue;
+          Site<R> B;
+          staged_site<R>(l[j], B);
+          site_force<R>(A, P, mui, B, l[j].mu, F);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) F[k] = group_sum<kClG>(F[k]);
+      if (lane == 0 && i < n)
         for (int k = 0; k < 3; ++k) a.forces[3 * (size_t)(base + i) + k] = kCoulomb * F[k];
     }
   }
