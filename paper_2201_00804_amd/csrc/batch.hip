@@ -7,7 +7,7 @@
 // A cluster is small (at most kClSmall sites) or large, by its own size:
 //
 //   small: one workgroup does everything, records and pair coefficients in
-//          LDS (k_cl_small, or beside the large solves);
+//          LDS (k_cl_small, or beside the large solves: small_apart);
 //   large: k_cl_prep  (site records, polarizable compaction),
 //          k_cl_field (16 sites per workgroup and step: field and E_elec;
 //                      other workgroups of the launch fill the table of
@@ -50,6 +50,32 @@ constexpr int kClMaxPol = SIBFA_BATCH_MAX_POLARIZABLE;
 // table in LDS holds 40 polarizable sites (25 KB; more are re-evaluated).
 constexpr int kClSmall = 64;
 constexpr int kClSmallTable = 40;
+// Do a batch's small clusters run in k_cl_small, before the large ones, or
+// beside the large solves?  A solve's workgroup has all registers of a CU, so
+// one cluster per CU at a time there and a small one takes a third longer (its
+// registers spill); k_cl_small takes two per CU but then the solves wait.  ns
+// small and nl large clusters, cs and cl the sums of their costs (cluster_cost)
+// and ml the largest: 256 CUs, and half a small cluster for the last round.
+// Calls beside / apart (FP64): 1,000 of 2 to 8 waters and one of 64 380 / 431 us,
+// and one of 13 359 / 311; 3,000 and one of 64 860 / 704; 200 of 8 to 12 waters
+// and 200 of 13 308 / 276; 1,000 of those and 4 of 128 691 / 861.
+struct BatchCost {
+  int ns, nl, cs, cl, ml;
+};
+// microseconds of a cluster of n sites, roughly
+__host__ __device__ inline int cluster_cost(int n) {
+  return n <= kClSmall ? 25 + n : 40 + n / 2;
+}
+__host__ __device__ inline bool small_apart(const BatchCost& b) {
+  constexpr int kCUs = 256;
+  if (b.nl == 0 || b.ns == 0) return b.nl == 0;
+  if (b.ns + b.nl <= kCUs) return false;
+  const int each = b.cs / b.ns, mean = (b.cl + b.cs / 3 * 4) / kCUs + each * 2 / 3;
+  const int beside = mean > b.ml ? mean : b.ml;
+  const int solves = b.cl / kCUs > b.ml ? b.cl / kCUs : b.ml;
+  const int first = b.cs / (2 * kCUs) > each ? b.cs / (2 * kCUs) : each;
+  return solves + first < beside;
+}
 static_assert(kClMaxPol <= kClSolveBlock, "one thread per polarizable site of the large solve");
 static_assert(kClSmall <= kClBlock, "one thread per site of a small cluster");
 
@@ -58,9 +84,12 @@ struct ClusterArgs {
   int nsites;           // sites in the caller arrays (and scratch capacity)
   const int* off;       // [nclusters + 1] site offsets into the caller arrays
   const int* warm;      // [nclusters] 1: start from mu, or nullptr
-  // clusters the large kernels are launched for, or nullptr: every cluster
-  // (those of the other class are skipped)
+  // clusters the large kernels are launched for, -1 after the last
   const int* large;
+  // where k_cl_prep writes that list and whether the small clusters run apart,
+  // if the host does not know the sizes, or nullptr
+  int* list;
+  int* apart;
   // start of each cluster's coefficient table in pairs, or -1 (nullptr: no
   // cluster has one)
   const long long* coef_off;
@@ -108,10 +137,11 @@ __device__ __forceinline__ bool cluster_range(const ClusterArgs& a, int c, int& 
   return base >= 0 && n >= 1 && n <= kClMaxSites && end <= a.nsites;
 }
 
-// The k-th cluster of a launch of the large kernels; false: skip it.
-__device__ __forceinline__ bool large_cluster(const ClusterArgs& a, int k, int& c, int& base,
-                                              int& n) {
-  c = a.large ? a.large[k] : k;
+// The k-th of count entries of the list of large clusters, -1 past the last.
+__device__ __forceinline__ int cluster_at(const ClusterArgs& a, int k, int count) {
+  return k < count ? a.large[k] : -1;
+}
+__device__ __forceinline__ bool large_cluster(const ClusterArgs& a, int c, int& base, int& n) {
   return cluster_range(a, c, base, n) && n > kClSmall;
 }
 
@@ -894,22 +924,61 @@ __device__ __forceinline__ void small_clusters(const ClusterArgs& a, SmallLds<R>
   }
 }
 
-// A batch without large clusters.  700 clusters of 2 to 8 waters (FP64):
-// 104 us for the whole call, against 192 us with one launch per stage,
-// dipole coefficients re-evaluated in every product and records gathered
-// from memory; one dimer 39 us against 58.
+// The small clusters of a batch in a launch of their own.  700 clusters of 2
+// to 8 waters (FP64): 104 us for the whole call, against 192 us with one launch
+// per stage, dipole coefficients re-evaluated in every product and records
+// gathered from memory; one dimer 39 us against 58.
 template <typename R>
 __global__ __launch_bounds__(kClBlock) void k_cl_small(ClusterArgs a) {
   __shared__ SmallLds<R> l;
+  if (a.apart && !*a.apart) return;
   small_clusters<R>(a, l, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------- large clusters
+// The large clusters of the batch in order, -1 after the last, and whether the
+// small ones run apart, by one workgroup.
+__device__ __forceinline__ void list_large(const ClusterArgs& a, int* wcount) {
+  constexpr int W = kClBlock / 64;
+  __shared__ BatchCost sum;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (t == 0) sum = BatchCost{};
+  int total = 0;
+  for (int c0 = 0; c0 < a.nclusters; c0 += kClBlock) {
+    const int c = c0 + t;
+    int base, n;
+    const bool on = c < a.nclusters && cluster_range(a, c, base, n), big = on && n > kClSmall;
+    const unsigned long long m = __ballot(big);
+    __syncthreads();
+    if (lane == 0) wcount[w] = __popcll(m);
+    if (on) {
+      atomicAdd(big ? &sum.nl : &sum.ns, 1);
+      atomicAdd(big ? &sum.cl : &sum.cs, cluster_cost(n));
+      if (big) atomicMax(&sum.ml, cluster_cost(n));
+    }
+    __syncthreads();
+    int before = total;
+    for (int k = 0; k < w; ++k) before += wcount[k];
+    if (big) a.list[lanes_below(m, before)] = c;
+    for (int k = 0; k < W; ++k) total += wcount[k];
+  }
+  for (int k = total + t; k < a.nclusters; k += kClBlock) a.list[k] = -1;
+  if (t == 0) *a.apart = small_apart(sum) ? 1 : 0;
+}
+
+// Clusters of a batch whose sizes the host does not know (a.list) are all
+// looked at, and the last workgroup writes the list for the other kernels.
 __global__ __launch_bounds__(kClBlock) void k_cl_prep(ClusterArgs a, int count) {
   __shared__ int wcount[kClBlock / 64], bad;
-  for (int b = blockIdx.x; b < count; b += gridDim.x) {
-    int c, base, n;
-    if (!large_cluster(a, b, c, base, n)) continue;
+  int nwg = gridDim.x;
+  if (a.list && (int)blockIdx.x == --nwg) {
+    list_large(a, wcount);
+    return;
+  }
+  for (int b = blockIdx.x; b < count; b += nwg) {
+    const int c = a.list ? b : a.large[b];
+    int base, n;
+    if (!large_cluster(a, c, base, n)) continue;
     __syncthreads();
     if (threadIdx.x == 0) bad = 0;
     const int np = cluster_records(a, base, n, a.rec + 4 * (size_t)base, a.polsite + base,
@@ -982,9 +1051,9 @@ template <typename R>
 __global__ __launch_bounds__(kClBlock) void k_cl_field(ClusterArgs a, int count) {
   __shared__ StagedSite<R> l[kClStage];
   const int t = threadIdx.x, slot = t / kClG, lane = t % kClG;
-  for (int b = blockIdx.x; b < count; b += gridDim.x) {
-    int c, base, n;
-    if (!large_cluster(a, b, c, base, n)) continue;
+  for (int b = blockIdx.x, c; (c = cluster_at(a, b, count)) >= 0; b += gridDim.x) {
+    int base, n;
+    if (!large_cluster(a, c, base, n)) continue;
     const double4* rec = a.rec + 4 * (size_t)base;
     if (blockIdx.z == 0) {
       for (int i0 = blockIdx.y * kClTile; i0 < n; i0 += gridDim.y * kClTile) {
@@ -1071,6 +1140,7 @@ __global__ __launch_bounds__(kClSolveBlock) void k_cl_solve(ClusterArgs a, int c
   __shared__ __align__(32) char lds[kLds];
   const int nlarge = gridDim.x - nsmall;
   if ((int)blockIdx.x >= nlarge) {
+    if (a.apart && *a.apart) return;
     if (threadIdx.x < kClBlock)
       small_clusters<R>(a, *reinterpret_cast<SmallLds<R>*>(lds), blockIdx.x - nlarge, nsmall);
     return;
@@ -1081,9 +1151,9 @@ __global__ __launch_bounds__(kClSolveBlock) void k_cl_solve(ClusterArgs a, int c
   const BlockSum<kClSolveBlock> bsum{l.sh};
   constexpr int nslot = kClSolveBlock / kClG;
   const int t = threadIdx.x, slot = t / kClG, lane = t % kClG;
-  for (int b = blockIdx.x; b < count; b += nlarge) {
-    int c, base, n;
-    if (!large_cluster(a, b, c, base, n)) continue;
+  for (int b = blockIdx.x, c; (c = cluster_at(a, b, count)) >= 0; b += nlarge) {
+    int base, n;
+    if (!large_cluster(a, c, base, n)) continue;
     const long long off = a.coef_off ? a.coef_off[c] : -1;
     if ((off >= 0) != TAB) continue;
     const int np = a.npol[c], st0 = a.status[c];
@@ -1149,9 +1219,9 @@ template <typename R>
 __global__ __launch_bounds__(kClBlock) void k_cl_force(ClusterArgs a, int count) {
   __shared__ StagedSite<R> l[kClStage];
   const int t = threadIdx.x, slot = t / kClG, lane = t % kClG;
-  for (int b = blockIdx.x; b < count; b += gridDim.x) {
-    int c, base, n;
-    if (!large_cluster(a, b, c, base, n)) continue;
+  for (int b = blockIdx.x, c; (c = cluster_at(a, b, count)) >= 0; b += gridDim.x) {
+    int base, n;
+    if (!large_cluster(a, c, base, n)) continue;
     const bool zero = a.status[c] == (int)SIBFA_E_ARG;
     const double* gmu = a.mu + 3 * (size_t)base;
     const double4* rec = a.rec + 4 * (size_t)base;
@@ -1198,7 +1268,7 @@ constexpr size_t kNaClusters = SIBFA_BATCH_NOALLOC_MAX_CLUSTERS;
 constexpr size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr size_t kNaBytes =
     a256((kNaClusters + 1) * sizeof(int)) + 3 * a256(kNaClusters * sizeof(int)) +
-    a256(kNaClusters * sizeof(long long)) + 2 * a256(kNaSites * sizeof(int)) +
+    a256(kNaClusters * sizeof(long long)) + a256(sizeof(int)) + 2 * a256(kNaSites * sizeof(int)) +
     a256(kNaSites * sizeof(double)) + 5 * a256(kNaSites * sizeof(double4));
 }  // namespace
 
@@ -1262,6 +1332,7 @@ size_t carve(char* base, size_t sites, size_t clusters, ClusterArgs* a) {
   char* warm = take(clusters * sizeof(int));
   char* large = take(clusters * sizeof(int));
   char* npol = take(clusters * sizeof(int));
+  char* apart = take(sizeof(int));
   char* polsite = take(sites * sizeof(int));
   char* prank = take(sites * sizeof(int));
   char* usite = take(sites * sizeof(double));
@@ -1273,6 +1344,7 @@ size_t carve(char* base, size_t sites, size_t clusters, ClusterArgs* a) {
     a->warm = reinterpret_cast<int*>(warm);
     a->large = reinterpret_cast<int*>(large);
     a->npol = reinterpret_cast<int*>(npol);
+    a->apart = reinterpret_cast<int*>(apart);
     a->polsite = reinterpret_cast<int*>(polsite);
     a->prank = reinterpret_cast<int*>(prank);
     a->usite = reinterpret_cast<double*>(usite);
@@ -1288,29 +1360,31 @@ size_t carve(char* base, size_t sites, size_t clusters, ClusterArgs* a) {
     if (e_ != hipSuccess) return bfail(b, SIBFA_E_DEVICE, hipGetErrorString(e_));   \
   } while (0)
 
-// small: the batch may hold small clusters; large: clusters the large
-// kernels run over; bare: some of them have no coefficient table; tiles:
-// workgroups per large cluster (any number >= 1).
+// Which kernels a batch needs: gs workgroups for its small clusters, run apart
+// or beside the large solves (both: the device decides, a.apart), and gx for the
+// `large` entries of the list of large ones, tiles for each of them; bare: some
+// have no coefficient table.  Any numbers of workgroups >= 1 give the same
+// results.
+struct BatchPlan {
+  bool apart = false, beside = false, bare = false;
+  int gs = 0, large = 0, gx = 0, tiles = 1;
+};
 template <typename R>
-void launch_batch(const ClusterArgs& a, bool small, int large, bool bare, int tiles,
-                  hipStream_t st) {
-  const dim3 b(kClBlock);
-  const int gs = small ? std::min(a.nclusters, 16384) : 0;
-  if (large <= 0) {
-    if (gs) hipLaunchKernelGGL(k_cl_small<R>, dim3(gs), b, 0, st, a);
-    return;
-  }
-  const int gx = std::min(large, 16384);
-  hipLaunchKernelGGL(k_cl_prep, dim3(gx), b, 0, st, a, large);
-  hipLaunchKernelGGL(k_cl_field<R>, dim3(gx, tiles, a.coef_off ? 2 : 1), b, 0, st, a, large);
-  const dim3 bs(kClSolveBlock);
+void launch_batch(const ClusterArgs& a, const BatchPlan& p, hipStream_t st) {
+  const dim3 b(kClBlock), bs(kClSolveBlock);
+  if (p.large > 0)
+    hipLaunchKernelGGL(k_cl_prep, dim3(a.list ? p.large + 1 : p.gx), b, 0, st, a, p.large);
+  if (p.apart) hipLaunchKernelGGL(k_cl_small<R>, dim3(p.gs), b, 0, st, a);
+  if (p.large <= 0) return;
+  hipLaunchKernelGGL(k_cl_field<R>, dim3(p.gx, p.tiles, a.coef_off ? 2 : 1), b, 0, st, a, p.large);
+  const int gs = p.beside ? p.gs : 0;
   if (a.coef_off)
-    hipLaunchKernelGGL((k_cl_solve<R, true>), dim3(gx + gs), bs, 0, st, a, large, gs);
-  if (bare) {
+    hipLaunchKernelGGL((k_cl_solve<R, true>), dim3(p.gx + gs), bs, 0, st, a, p.large, gs);
+  if (p.bare) {
     const int g2 = a.coef_off ? 0 : gs;   // the small clusters run once
-    hipLaunchKernelGGL((k_cl_solve<R, false>), dim3(gx + g2), bs, 0, st, a, large, g2);
+    hipLaunchKernelGGL((k_cl_solve<R, false>), dim3(p.gx + g2), bs, 0, st, a, p.large, g2);
   }
-  if (a.forces) hipLaunchKernelGGL(k_cl_force<R>, dim3(gx, tiles), b, 0, st, a, large);
+  if (a.forces) hipLaunchKernelGGL(k_cl_force<R>, dim3(p.gx, p.tiles), b, 0, st, a, p.large);
 }
 
 // Bound on the coefficient tables kept with an executor: 512 MB hold the
@@ -1421,6 +1495,7 @@ sibfa_status sibfa_batch_clusters(sibfa_batch b, int n_clusters, const int* site
   int* h_warm = reinterpret_cast<int*>(b->h_stage + o_warm);
   int* h_large = reinterpret_cast<int*>(b->h_stage + o_large);
   int nlarge = 0, maxn = 0;
+  BatchCost cost{};
   bool bare = false;   // large clusters without a table
   size_t pairs = 0;
   for (int c = 0; c < n_clusters; ++c) {
@@ -1428,7 +1503,14 @@ sibfa_status sibfa_batch_clusters(sibfa_batch b, int n_clusters, const int* site
     h_warm[c] = warm_start ? (warm_start[c] != 0) : 0;
     const int nc = site_offsets[c + 1] - site_offsets[c];
     h_coef[c] = -1;
-    if (nc <= kClSmall) continue;
+    if (nc <= kClSmall) {
+      ++cost.ns;
+      cost.cs += cluster_cost(nc);
+      continue;
+    }
+    ++cost.nl;
+    cost.cl += cluster_cost(nc);
+    cost.ml = std::max(cost.ml, cluster_cost(nc));
     h_large[nlarge++] = c;
     maxn = std::max(maxn, nc);
     const size_t np = std::min(nc, kClMaxPol);
@@ -1478,9 +1560,17 @@ sibfa_status sibfa_batch_clusters(sibfa_batch b, int n_clusters, const int* site
   a.iters = iterations;
   a.rms = rms_debye;
   a.status = status;
-  const int tiles = (maxn + kClTile - 1) / kClTile;
-  if (mix) launch_batch<float>(a, nlarge < n_clusters, nlarge, bare, tiles, b->stream);
-  else launch_batch<double>(a, nlarge < n_clusters, nlarge, bare, tiles, b->stream);
+  a.apart = nullptr;   // decided here
+  BatchPlan p;
+  p.gs = std::min(n_clusters, 16384);
+  p.apart = cost.ns > 0 && small_apart(cost);
+  p.beside = cost.ns > 0 && !p.apart;
+  p.large = nlarge;
+  p.gx = std::min(nlarge, 16384);
+  p.bare = bare;
+  p.tiles = (maxn + kClTile - 1) / kClTile;
+  if (mix) launch_batch<float>(a, p, b->stream);
+  else launch_batch<double>(a, p, b->stream);
   BHIP(hipGetLastError());
   return SIBFA_OK;
 }
@@ -1534,7 +1624,19 @@ extern "C" sibfa_status sibfa_batch_clusters_noalloc(
   carve(static_cast<char*>(base), kNaSites, kNaClusters, &a);
   a.off = site_offsets;   // the caller's device arrays, checked per cluster
   a.warm = warm_start;
-  a.large = nullptr;      // sizes are known on the device only
+  // Sizes are known on the device only: k_cl_prep lists the large clusters, of
+  // which at most gx fit n_sites (ranges that overlap, which could be more,
+  // wait their turn).  Small clusters look in both places where they may run.
+  BatchPlan p;
+  p.gs = n_clusters;
+  p.apart = true;
+  p.large = n_sites > kClSmall ? n_clusters : 0;
+  p.beside = p.large > 0;
+  p.gx = std::max(1, std::min(n_clusters, n_sites / (kClSmall + 1)));
+  p.bare = true;
+  p.tiles = std::min(kClMaxSites / kClTile, 8);
+  a.list = p.large > 0 ? const_cast<int*>(a.large) : nullptr;
+  if (p.large == 0) a.apart = nullptr;
   a.coef_off = nullptr;   // no room for tables
   a.nclusters = n_clusters;
   a.nsites = n_sites;
@@ -1556,8 +1658,7 @@ extern "C" sibfa_status sibfa_batch_clusters_noalloc(
   a.rms = rms_debye;
   a.status = status;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  const int tiles = std::min(kClMaxSites / kClTile, 8);
-  if (params->precision == SIBFA_MIXED) launch_batch<float>(a, true, n_clusters, true, tiles, st);
-  else launch_batch<double>(a, true, n_clusters, true, tiles, st);
+  if (params->precision == SIBFA_MIXED) launch_batch<float>(a, p, st);
+  else launch_batch<double>(a, p, st);
   return hipGetLastError() == hipSuccess ? SIBFA_OK : SIBFA_E_DEVICE;
 }
