@@ -1141,8 +1141,13 @@ __global__ __launch_bounds__(kClSolveBlock) void k_cl_solve(ClusterArgs a, int c
   const int nlarge = gridDim.x - nsmall;
   if ((int)blockIdx.x >= nlarge) {
     if (a.apart && *a.apart) return;
-    if (threadIdx.x < kClBlock)
-      small_clusters<R>(a, *reinterpret_cast<SmallLds<R>*>(lds), blockIdx.x - nlarge, nsmall);
+    // The other wavefronts end here, by a scalar branch, before the barriers of
+    // the first: s_barrier waits for the wavefronts of a workgroup that have not
+    // ended, so those synchronise among themselves.  Kept alive to come to every
+    // barrier instead, they cost 40 + 40 clusters of 2 to 12 and of 20 waters 164
+    // -> 180 us (mixed).
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x) >= kClBlock) return;
+    small_clusters<R>(a, *reinterpret_cast<SmallLds<R>*>(lds), blockIdx.x - nlarge, nsmall);
     return;
   }
   SolveLds<R>& l = *reinterpret_cast<SolveLds<R>*>(lds);
