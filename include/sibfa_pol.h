@@ -423,11 +423,14 @@ sibfa_status sibfa_get_profile(sibfa_ctx ctx, sibfa_profile* out);
  *
  * Same mathematics as a cluster context (direct sums, no cutoff; the
  * permanent field, the PCG solve of T mu = E (Eq. 18), E_pol (Eq. 19),
- * E_elec and forces), for many clusters in one call: one workgroup owns one
- * cluster and keeps its whole solve on the device, so a batch costs three
- * kernel launches and no host synchronisation.  A cluster's results are
- * bitwise independent of the other clusters in the batch.  The batched
- * solve uses the diagonal preconditioner (params.precond is not read).
+ * E_elec and forces), for many clusters in one call.  One workgroup does all
+ * of a cluster of at most 64 sites; field and forces of a larger one are spread
+ * over many, its solve is one workgroup's.  Everything stays on the device: a
+ * batch is one to six kernel launches (one if all clusters are small), without
+ * a host synchronisation once the executor's memory has its size.  A cluster's
+ * results are bitwise independent of the other clusters in the batch and of the
+ * executor's memory.  The batched solve uses the diagonal preconditioner
+ * (params.precond is not read).
  *
  * Limits per cluster: at most SIBFA_BATCH_MAX_SITES sites and
  * SIBFA_BATCH_MAX_POLARIZABLE polarizable sites (larger systems use a
@@ -439,8 +442,17 @@ sibfa_status sibfa_get_profile(sibfa_ctx ctx, sibfa_profile* out);
 typedef struct sibfa_batch_s* sibfa_batch;
 
 /* A batch executor on `device`, enqueuing on `hip_stream`; alloc/free as
- * for sibfa_create.  It owns scratch memory that grows to the largest batch
- * seen (about 240 bytes per site) and pinned staging for the offsets. */
+ * for sibfa_create.  It owns, until it is destroyed,
+ *  - scratch memory for the largest batch seen (about 180 bytes per site, up to
+ *    twice that after growing) and pinned staging for the offsets;
+ *  - tables of pair coefficients for clusters of more than 64 sites: 16 bytes
+ *    (FP64) or 24 (mixed) times the square of min(sites,
+ *    SIBFA_BATCH_MAX_POLARIZABLE) for each, 1.6 or 2.5 MB at 320 sites, for
+ *    the largest batch seen (up to twice that after growing) but never more
+ *    than 512 MB in all.  Clusters past the bound, or for whose tables alloc_fn
+ *    (hipMalloc) returned NULL, are evaluated without, more slowly and to the
+ *    same bits; a size that was refused is not asked for again.
+ * Growing either waits for the stream. */
 sibfa_status sibfa_batch_create(sibfa_batch* out, int device, void* hip_stream,
                                 sibfa_alloc_fn alloc_fn, sibfa_free_fn free_fn,
                                 void* user);
@@ -460,7 +472,8 @@ const char* sibfa_batch_last_error(sibfa_batch b);
  *  params (HOST): thole_a, tol_debye, max_iter and precision are used;
  *    the Ewald/PME fields are ignored.
  * Outputs (DEVICE), written when the batch's kernels complete on the
- * stream (the call itself only enqueues work):
+ * stream (the call itself only enqueues work, unless the executor's memory
+ * has to grow):
  *  mu [n][3] (also the warm-start input), forces [n][3] or NULL,
  *  e_pol, e_elec [n_clusters] kcal/mol, iterations [n_clusters],
  *  rms_debye [n_clusters] (true residual), status [n_clusters]:

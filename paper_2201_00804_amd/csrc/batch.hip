@@ -1288,9 +1288,10 @@ struct sibfa_batch_s {
   std::string err;
   size_t cap_sites = 0, cap_clusters = 0;
   void* scratch = nullptr;   // one device allocation holding every array
-  // coefficient tables of the large clusters, at most kClTableBytes in all
+  // coefficient tables of the large clusters, at most kClTableBytes in all;
+  // table_refused: the smallest size that there was no memory for (0: none)
   void* table = nullptr;
-  size_t table_bytes = 0;
+  size_t table_bytes = 0, table_refused = 0;
   // pinned staging of table starts, offsets, warm flags and large clusters
   char* h_stage = nullptr;
   size_t h_cap = 0;          // bytes
@@ -1392,10 +1393,37 @@ void launch_batch(const ClusterArgs& a, const BatchPlan& p, hipStream_t st) {
   if (a.forces) hipLaunchKernelGGL(k_cl_force<R>, dim3(p.gx, p.tiles), b, 0, st, a, p.large);
 }
 
-// Bound on the coefficient tables kept with an executor: 512 MB hold the
-// FP64 tables of 850 clusters of 64 waters; clusters past it re-evaluate
-// their coefficients in every product.
+// Bound on the coefficient tables kept with an executor.  They are reserved by
+// the clusters' sites (the host does not know how many are polarizable, 192 of
+// the 320 of 64 waters): 512 MB for 327 clusters of 64 waters in FP64 and 218
+// in mixed precision.  Clusters past the bound re-evaluate their coefficients in
+// every product.
 constexpr size_t kClTableBytes = (size_t)512 << 20;
+
+// Room for `bytes` of tables, or as much of it as there is memory for: more
+// than that, to grow into, the exact size, or the table that there was.
+// Growing waits for the stream, where an earlier batch may read the old table,
+// so a size that was refused is not asked for again.
+sibfa_status grow_table(sibfa_batch b, size_t bytes) {
+  if (bytes <= b->table_bytes || (b->table_refused && bytes >= b->table_refused))
+    return SIBFA_OK;
+  BHIP(hipStreamSynchronize(b->stream));
+  const size_t old = b->table_bytes;
+  bfree(b, b->table);
+  b->table = nullptr;
+  b->table_bytes = 0;
+  size_t refused = 0;
+  for (size_t want : {std::min(kClTableBytes, std::max(bytes, 2 * old)), bytes, old}) {
+    if (want == 0 || want == refused) continue;
+    if ((b->table = balloc(b, want))) {
+      b->table_bytes = want;
+      break;
+    }
+    refused = want;
+  }
+  if (b->table_bytes < bytes) b->table_refused = bytes;
+  return SIBFA_OK;
+}
 
 }  // namespace
 
@@ -1501,8 +1529,7 @@ sibfa_status sibfa_batch_clusters(sibfa_batch b, int n_clusters, const int* site
   int* h_large = reinterpret_cast<int*>(b->h_stage + o_large);
   int nlarge = 0, maxn = 0;
   BatchCost cost{};
-  bool bare = false;   // large clusters without a table
-  size_t pairs = 0;
+  size_t wanted = 0;   // pairs of all tables
   for (int c = 0; c < n_clusters; ++c) {
     h_off[c] = site_offsets[c];
     h_warm[c] = warm_start ? (warm_start[c] != 0) : 0;
@@ -1519,28 +1546,28 @@ sibfa_status sibfa_batch_clusters(sibfa_batch b, int n_clusters, const int* site
     h_large[nlarge++] = c;
     maxn = std::max(maxn, nc);
     const size_t np = std::min(nc, kClMaxPol);
-    if ((pairs + np * np) * pair_bytes <= kClTableBytes) {
+    if ((wanted + np * np) * pair_bytes <= kClTableBytes) wanted += np * np;
+  }
+  h_off[n_clusters] = site_offsets[n_clusters];
+  const sibfa_status grown = grow_table(b, wanted * pair_bytes);
+  if (grown != SIBFA_OK) return grown;
+  bool bare = false;   // large clusters without a table
+  size_t pairs = 0;
+  for (int k = 0; k < nlarge; ++k) {
+    const int c = h_large[k];
+    const size_t np = std::min(site_offsets[c + 1] - site_offsets[c], kClMaxPol);
+    if ((pairs + np * np) * pair_bytes <= std::min(b->table_bytes, kClTableBytes)) {
       h_coef[c] = (long long)pairs;
       pairs += np * np;
     } else {
       bare = true;
     }
   }
-  h_off[n_clusters] = site_offsets[n_clusters];
-  if (pairs * pair_bytes > b->table_bytes) {
-    BHIP(hipStreamSynchronize(b->stream));
-    bfree(b, b->table);
-    const size_t want = std::min(kClTableBytes, std::max(pairs * pair_bytes, 2 * b->table_bytes));
-    b->table_bytes = 0;
-    b->table = balloc(b, want);
-    if (b->table) b->table_bytes = want;
-  }
-  if (pairs * pair_bytes <= b->table_bytes && pairs > 0) {
+  if (pairs > 0) {
     a.coef = static_cast<double2*>(b->table);
     a.coef32 = mix ? reinterpret_cast<float2*>(a.coef + pairs) : nullptr;
   } else {
     a.coef_off = nullptr;   // none needed, or no memory for them
-    bare = true;
   }
   BHIP(hipMemcpyAsync(b->scratch, b->h_stage, nlarge > 0 ? need : o_warm + n_clusters * sizeof(int),
                       hipMemcpyHostToDevice, b->stream));
