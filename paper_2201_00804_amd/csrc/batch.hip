@@ -133,8 +133,8 @@ struct ClusterArgs {
 __device__ __forceinline__ bool cluster_range(const ClusterArgs& a, int c, int& base, int& n) {
   base = a.off[c];
   const int end = a.off[c + 1];
-  n = end - base;
-  return base >= 0 && n >= 1 && n <= kClMaxSites && end <= a.nsites;
+  n = base >= 0 && end > base ? end - base : 0;   // no overflow: both are >= 0
+  return n >= 1 && n <= kClMaxSites && end <= a.nsites;
 }
 
 // The k-th of count entries of the list of large clusters, -1 past the last.
