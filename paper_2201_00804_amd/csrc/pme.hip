@@ -138,8 +138,8 @@ __device__ __forceinline__ void spread_weights(R w, R th[ND + 1][P]) {
 // their derivatives per axis, three lanes per site); meanwhile the first
 // walks the chunk before, site by site in order, and adds each site's p^3
 // points to the tile, one point per lane (two rounds at p = 5): a read, the
-// three-axis product and a write per point, no atomics (a wave's LDS
-// accesses are in order).  Bound by instruction issue of the first wave,
+// three-axis product and a write per point, no atomics: a wave's LDS accesses
+// are carried out in order, and wave_sync() keeps the compiler to it.  Bound by instruction issue of the first wave,
 // about 36 per site and one every five cycles.  A thread per tile column
 // instead, its z values in registers, spent 5% of its multiply-adds on
 // points inside the site's support and 70 instructions of three waves per
@@ -270,11 +270,9 @@ __global__ __launch_bounds__(128) void k_spread_tile(SysView s, PmeView pm, cons
       continue;
     }
     const SpreadChunk<R, P, FULL>& c = chunk[buf];
-#pragma unroll 2
-    for (int j = 0; j < n; ++j) {
+    auto value = [&](int j, R v[NR]) {
+#pragma clang fp contract(off)
       const R* A = c.amp[j];
-      const int base = c.top[j];
-      R v[NR];
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
         const R* X = c.wt[j][0][dx[r]];
@@ -293,11 +291,30 @@ __global__ __launch_bounds__(128) void k_spread_tile(SysView s, PmeView pm, cons
           v[r] = fma_(U0, Z[0], U1 * Z[1]);
         }
       }
+    };
+    // other lanes wrote these points for the site before: its writes come first
+    auto add = [&](int base, const R v[NR]) {
+      wave_sync();
       R t[NR];
 #pragma unroll
       for (int r = 0; r < NR; ++r) t[r] = tile[base - off[r]];
 #pragma unroll
       for (int r = 0; r < NR; ++r) tile[base - off[r]] = t[r] + v[r];
+    };
+    // two sites' weights are read before the first touches the tile
+    int j = 0;
+    for (; j + 1 < n; j += 2) {
+      R v0[NR], v1[NR];
+      const int b0 = c.top[j], b1 = c.top[j + 1];
+      value(j, v0);
+      value(j + 1, v1);
+      add(b0, v0);
+      add(b1, v1);
+    }
+    if (j < n) {
+      R v[NR];
+      value(j, v);
+      add(c.top[j], v);
     }
   }
   __syncthreads();
