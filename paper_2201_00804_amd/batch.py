@@ -1,6 +1,6 @@
 """Python binding of the batched-cluster executor (sibfa_batch_*): many
-independent gas-phase clusters evaluated in one call, one workgroup per
-cluster.  Only marshalling happens here; the work runs in the HIP library.
+independent gas-phase clusters evaluated in one call, the small ones by one
+workgroup each.  Only marshalling happens here; the work runs in the HIP library.
 """
 import ctypes
 

@@ -1122,9 +1122,9 @@ template <> __device__ __forceinline__ auto coef_table<float>(const ClusterArgs&
 // last nsmall run the batch's small clusters beside them with their first
 // kClBlock threads, since the solves leave most of the GPU idle.  A solve is
 // a chain of matrix products by one workgroup: with 48 clusters of 2 to 64
-// waters (mixed precision) the launch takes 195 us, against 680 us when 256
-// threads re-evaluated the coefficients in every product (field 350 -> 58,
-// forces 510 -> 56 us), and the whole call 1.57 -> 0.32 ms.
+// waters (mixed precision) the launch takes 185 us, against 680 us when 256
+// threads re-evaluated the coefficients in every product (field 350 -> 23,
+// forces 510 -> 30 us), and the whole call 1.57 -> 0.25 ms.
 template <typename R>
 struct SolveLds {
   double4 lpos[kClMaxPol], lv[kClMaxPol];

@@ -432,9 +432,12 @@ __global__ __launch_bounds__(kBlock) void k_fft_x_c2r(PmeView pm, int nl) {
 // matvec to drain; 256 threads leave the plane itself too slow).
 constexpr int kPlaneThreads = 512;
 // Planes of up to kFoldPlane points sum the spreading tiles themselves: one
-// launch less, 10.6 us instead of 3.8 + 9.8 (18^3 points, FP64) and 10.6
-// instead of 4.8 + 7.8 (48^3, FP32).  At 96^3 the 96 workgroups take as long as
-// the two kernels do (FP32: 55 us against 29 + 26) or longer (FP64: 75, 35 + 32).
+// launch and its gap (1 to 2 us) less, 10.6 us instead of 3.8 + 9.8 (18^3 points,
+// FP64) and 10.6 instead of 4.8 + 7.8 (48^3, FP32).  The gain ends about there:
+// 60^3 19.2 against 6.2 + 11.5 (FP64) and 15.2 against 5.9 + 10.2 (FP32), 64^3 21.3
+// against 9.8 + 12.6 and 15.6 against 6.4 + 10.2; at 72^3 36.1 against 14.6 + 15.6
+// and 23.3 against 9.5 + 13.8, at 96^3 the 96 workgroups take as long as the two
+// kernels (FP32: 55 us against 29 + 26) or longer (FP64: 75, 35 + 32).
 constexpr int kFoldPlane = 64 * 64;
 
 template <typename T, int NT, bool FOLD>

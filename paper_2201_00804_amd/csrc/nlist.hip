@@ -858,7 +858,9 @@ void launch_cellmax_reduce(const int4* cellmax, int count, int* out, hipStream_t
 // Wavefronts per cell: enough for kNlWaves in all, at most one per site of
 // an average cell; two up to twice kNlWaves cells, where one each are too few
 // rounds of the 5,120 that fit to even out (9,261 cells: 546 against 486 us;
-// three take 520, as every slice loads the cell's candidates).
+// three take 520, as every slice loads the cell's candidates).  One / two: 5,832
+// cells 335 / 307 us, 8,000 422 / 392, 13,824 617 / 591; at 17,576, past the line,
+// 747 / 711 in one run and 706 / 717 in another.
 int nlist_slices(int n, int ncell) {
   const int per_cell = (n + ncell - 1) / ncell;
   return std::max(1, std::min(per_cell, std::max(kNlWaves / ncell, ncell < 2 * kNlWaves ? 2 : 1)));

@@ -319,7 +319,7 @@ __global__ __launch_bounds__(kBlock) void k_perm(SysView s, Reduce red, double4*
         perm_pair<R, false>(s, i, j0, pi, Mi, xi, si, U, acc);
         perm_pair<R, false>(s, i, j1, pi, Mi, xi, si, U, acc);
       }
-    if (k < nf) perm_pair<R, false>(s, i, far[-k], pi, Mi, xi, si, U, acc);
+      if (k < nf) perm_pair<R, false>(s, i, far[-k], pi, Mi, xi, si, U, acc);
     }
   }
 #pragma unroll
@@ -1015,7 +1015,10 @@ static void matvec_recip_p(const SysView& s, const PmeView& pm, Reduce& red, con
                            double4* out, int dot_slot, bool mixed, hipStream_t st) {
   // one wavefront per workgroup while four leave CUs idle: the texture path
   // of each bounds its share (12,288 sites: 11.3 us with single loads and four,
-  // 5.6 us; with 96,000 sites rows and loads ahead alone 21.4 against 10.1)
+  // 5.6 us; with 96,000 sites rows and loads ahead alone 21.4 against 10.1).
+  // Four / one (FP64): 972 sites 6.9 / 5.6 us, 14,739 8.1 / 5.8, 41,472 7.8 / 7.4,
+  // 59,049 9.0 / 9.0; past the line the CUs are full with either, and which is
+  // ahead varies: 81,000 11.8 / 10.1, 128,625 15.9 / 16.6.
   const bool few = s.npol <= 256 * kBlock;
   const dim3 b(few ? 64 : kBlock), g((s.npol + b.x - 1) / b.x);
   if (mixed) hipLaunchKernelGGL((k_matvec_recip<float, P>), g, b, 0, st, s, pm, red, p, out, dot_slot);

@@ -317,7 +317,9 @@ void launch_direction(const SysView& s, const Reduce& red, int num, int den, con
 // bound by their launches and by each one's chain of totals, vectors and sums;
 // here one workgroup keeps the totals to itself (solves with it: 20 waters 428
 // -> 381 us, 80 487 -> 433, 300 764 -> 735, a box of 216 1282 -> 1206).  Past
-// kStepSites one CU takes longer over the vectors than the launch it saves.
+// kStepSites one CU takes longer over the vectors than the launch it saves (a
+// launch and its gap, 1 to 2 us): 972 sites 8.8 us against 4.7 + 5.2, 1,152 11.1
+// against 4.9 + 5.4, 3,003 18.8 against 4.8 + 5.5.
 // The block preconditioner stays with its own kernels: in one workgroup its
 // factors take as long (216 waters: 13.5 us against 7.5 + 5.2).  Every sum is
 // made in the order of the kernels this one stands for: a wavefront, the four

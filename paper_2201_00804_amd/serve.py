@@ -17,7 +17,7 @@ converged induced dipoles.  The server keeps work resident on the device:
     different boxes overlap on the device, each on its context's streams;
   * clusters are gathered into batches: every cluster pending when the
     cluster worker becomes free goes into one sibfa_batch_clusters call
-    (three launches for the whole batch), warm-started from the dipoles of
+    (a few launches for the whole batch), warm-started from the dipoles of
     the system's previous request when there was one.  A cluster system's
     multipoles, polarizabilities and last dipoles stay on the device; a
     request brings only its positions.
