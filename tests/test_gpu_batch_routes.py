@@ -89,3 +89,36 @@ def test_overlapping_ranges_are_all_solved():
     assert out["status"].tolist() == [0, -1, 0, -1, 0, -1, 0]
     assert torch.equal(out["mu"], one["mu"]) and torch.equal(out["forces"], one["forces"])
     assert torch.equal(out["e_pol"][::2], one["e_pol"].expand(4))
+
+
+@pytest.mark.parametrize("counts", [{2: 5}, {2: 900, 13: 4}, {2: 270, 64: 2}])
+def test_routes_under_capture(counts):
+    """The call without an executor recorded into a graph, on each route, and
+    replayed between other work on new positions: the eager call's bits."""
+    from paper_2201_00804_amd import _lib
+    from paper_2201_00804_amd.batch import concat_clusters
+    lib, systems = _lib.load(), _systems(counts)
+    prm = gpu_params(systems[0], tol=1e-9)
+    off, t = concat_clusters(systems, "cuda")
+    n, nc = off[-1], len(systems)
+    off_dev = torch.as_tensor(off, dtype=torch.int32, device="cuda")
+    out, ref = _outputs(n, nc, "cuda"), _outputs(n, nc, "cuda")
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        assert _noalloc(lib, off_dev, n, t, prm, out, st) == 0
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        assert _noalloc(lib, off_dev, n, t, prm, out, torch.cuda.current_stream()) == 0
+    rng = np.random.default_rng(4)
+    for k in range(3):
+        t["xyz"] += torch.as_tensor(rng.uniform(-0.01, 0.01, (n, 3)), device="cuda")
+        graph.replay()
+        torch.cuda.synchronize()
+        # the eager call shares the scratch: only after the replay
+        assert _noalloc(lib, off_dev, n, t, prm, ref, torch.cuda.current_stream()) == 0
+        torch.cuda.synchronize()
+        say(f"[batch routes] replay {k} of {nc} clusters")
+        for key in ("mu", "forces", "e_pol", "e_elec", "iters", "status"):
+            assert torch.equal(out[key], ref[key]), key
+        assert int(out["status"].abs().max()) == 0
